@@ -170,7 +170,8 @@ typedef struct {
     double xi;            /* slice position */
     double dxi;           /* step taken from this slice to the next */
     double vmax;          /* max |V_perp| after the push (Algorithm 1) */
-    int32_t vcycles[5];   /* V-cycles per field solve (psi, Ez, Bz, Bx, By); -1 if not tracked */
+    int32_t vcycles[5];   /* cycles per field solve (psi, Ez, Bz, Bx, By); -1 if not tracked: V-cycles,
+                             or iterations of the exact sine-transform solve (see wandqs_mg_solve) */
     double rel_resid[5];  /* final ||r||/||f|| per field; -1 if not tracked */
     int32_t flags;        /* bit 0: 1+psi <= 0 met */
     int32_t laser_vcycles; /* multigrid cycles of the envelope plane this slice advanced
@@ -304,7 +305,10 @@ wandqs_status wandqs_time_step(wandqs_ctx* ctx, double dt, int32_t n_slices,
  * NULL for Poisson; d_f (device [nrhs][N+1][N+1]); d_u (device, same shape)
  * holds the initial guess and receives the solution.  Uses the context's
  * mg_* settings; h_cycles / h_rel (host, may be NULL) receive the V-cycle count
- * and ||r||/||f|| per rhs.  Clobbers the context's multigrid scratch arrays and
+ * and ||r||/||f|| per rhs.  Poisson solves in the tolerance mode (mg_rtol > 0)
+ * with mg_max_cycles >= 16 on grids of 128^2 .. 2048^2 iterate u += L_h^-1 (f -
+ * L_h u) with an exact FP64 sine-transform solve of the finest grid instead of
+ * V-cycles, to the same stop rule; an iteration then counts as a cycle.  Clobbers the context's multigrid scratch arrays and
  * the stored fields used as initial guesses. */
 wandqs_status wandqs_mg_solve(wandqs_ctx* ctx, int32_t nrhs, const double* d_k2,
                               const double* d_f, double* d_u, int32_t* h_cycles, double* h_rel);

@@ -146,7 +146,7 @@ void set_sizes(wandqs_ctx* c, const wandqs_config* cfg, int32_t n_slices) {
         c->graphs_on = g && std::strcmp(g, "1") == 0;
     }
     const int t = (c->N + 15) / 16;  // norm partials: one per tile of the smallest tile size
-    c->max_tiles = t * t;
+    c->max_tiles = std::max(t * t, c->N);  // or one per interior row
     c->n_push_blocks = (int)((c->P + 255) / 256);
     c->n_scan_blocks = (c->N * c->N + 2047) / 2048;
     c->rec_cap = n_slices;
@@ -348,20 +348,29 @@ wandqs_status check_flags(wandqs_ctx* c) {
 
 // Tables of the exact coarse Poisson solves (the 64^2 sine matrices in float,
 // with double copies for the mixed form's FP64 coarsest-grid solve) and the
-// arrays of the fast sine transform solve on level 1.
+// arrays of the fast sine transform solves on level 1 and (top) on the finest
+// level, which take turns in the intermediates.
 template <class Take>
-void carve_dst(wandqs_ctx* c, Take&& take) {
+void carve_dst(wandqs_ctx* c, Take&& take, bool top) {
     const bool mixed = c->cfg.precision == WANDQS_MIXED;
     c->dst_S = (float*)take(sizeof(float) * 64 * 64);
     c->dst_M = (float*)take(sizeof(float) * 64 * 64);
     c->dst_S64 = mixed ? (double*)take(sizeof(double) * 64 * 64) : nullptr;
     c->dst_M64 = mixed ? (double*)take(sizeof(double) * 64 * 64) : nullptr;
+    top = top && wq::fst_top_used(c);
+    if (top || wq::fst_used(c)) {
+        const size_t n = c->lev[top ? 0 : 1].N;
+        for (int r = 0; r < 2; ++r) {
+            c->fst_t1[r] = (double*)take(sizeof(double) * (n - 1) * (n + 8));
+            c->fst_t2[r] = (double*)take(sizeof(double) * (n - 1) * (n + 8));
+        }
+    }
+    if (top) {
+        c->fst_top_tw = (double2*)take(sizeof(double2) * 2 * (size_t)c->N);
+        c->fst_top_s2 = (double*)take(sizeof(double) * (size_t)(c->N + 1));
+    }
     if (wq::fst_used(c)) {
         const size_t n1 = c->lev[1].N;
-        for (int r = 0; r < 2; ++r) {
-            c->fst_t1[r] = (double*)take(sizeof(double) * (n1 - 1) * wq::fst_ld(c));
-            c->fst_t2[r] = (double*)take(sizeof(double) * (n1 - 1) * wq::fst_ld(c));
-        }
         c->fst_tw = (double2*)take(sizeof(double2) * 2 * n1);
         c->fst_s2 = (double*)take(sizeof(double) * (n1 + 1));
     }
@@ -401,7 +410,7 @@ size_t wq::carve(wandqs_ctx* c, char* base) {
         c->k2levf = (float*)take(sizeof(float) * (size_t)tot);
         c->idlevf = (float*)take(sizeof(float) * (size_t)tot);
     }
-    carve_dst(c, take);
+    carve_dst(c, take, true);
     for (int l = 1; l <= c->lc; ++l) {
         Level& L = c->lev[l];
         for (int r = 0; r < 2; ++r) {
@@ -550,7 +559,7 @@ size_t wq::carve_solver(wandqs_ctx* c, char* base) {
         c->k2levf = (float*)take(sizeof(float) * (size_t)tot);
         c->idlevf = (float*)take(sizeof(float) * (size_t)tot);
     }
-    carve_dst(c, take);
+    carve_dst(c, take, false);
     for (int l = 1; l <= c->lc; ++l) {
         Level& L = c->lev[l];
         for (int r = 0; r < 2; ++r) {

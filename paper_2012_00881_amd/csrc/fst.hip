@@ -1,7 +1,9 @@
-// Exact Poisson solve on the level just below the finest by fast sine
-// transforms, FP64 (the coarse-grid correction of the Poisson V-cycles of
-// eqs. (12)-(15), Sec. III.B; the five-point operator of Sec. VII.B on a
-// uniform grid).
+// Exact Poisson solve by fast sine transforms, FP64, of eqs. (12)-(15), Sec.
+// III.B (the five-point operator of Sec. VII.B on a uniform grid): on the
+// finest level as the whole solve (TOP: iterations u += L_h^-1 (f - L_h u) of
+// the tolerance mode), and on the level just below the finest as the
+// coarse-grid correction of the Poisson V-cycles (fixed-cycle mode, grids
+// above 2048^2).
 //
 // With zero Dirichlet values the five-point Laplacian of an n x n-cell level
 // of spacing H has the eigenvectors sin(pi i k / n) sin(pi j l / n) (1 <= k, l
@@ -32,7 +34,9 @@
 // A first form with two rows packed into one complex FFT of length 2n (the
 // odd extensions; 256 threads and a barrier per stage) measured 9.7 / 6.6 /
 // 5.3 us for the y / x inverse / x passes at n = 512, this one 7.5 / 5.4 /
-// 5.4.
+// 5.4.  TOP at n = 1024, averaged over one and two right-hand sides: x 23.6,
+// y 23.2, x inverse 13.2 us (1.6, 1.1 and 2.9 TB/s of its bytes; the transposed
+// 16-byte writes bound the first two); at n = 512 6.8 / 7.3 / 4.8.
 #include <cstdio>
 
 #include "wq_common.h"
@@ -52,6 +56,11 @@ struct FstArgs {
     const double* s2;   // sin^2(pi k / (2n)), k <= n
     double lam;         // -4 / H^2
     double scale;       // (2 / n)^2
+    // TOP (the whole solve on the finest level): 1 / H^2 and the norm sums of
+    // the incoming iterate, [3 r + q][nblk] with one entry per row
+    double ih2;
+    double* norm_part;
+    int nblk;
 };
 
 // In-register DFT of length R (2 or 4), natural order in and out.
@@ -83,6 +92,47 @@ __device__ __forceinline__ void dft(double (&re)[R], double (&im)[R]) {
 
 // LDS slot of element i of a padded buffer
 __device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }
+
+__device__ __forceinline__ double2 ld2(const double* p) { return *reinterpret_cast<const double2*>(p); }
+
+// TOP, x pass: the residual f - L_h u of one row (u and f point at it) into V
+// (padded; V[0] = 0) and the lane's sums of r^2, f^2, u^2 over its nodes.
+// Lane l takes the pairs (2m, 2m + 1), m = l + 64 q, in batches whose loads are
+// all in flight together (row starts are 64-byte aligned: 16-byte loads).
+template <int PER>
+__device__ __forceinline__ void residual_row(const double* u, const double* f, int pitch, double ih2,
+                                             double* V, double (&s)[3]) {
+    constexpr int CH = PER < 4 ? PER : 4;
+    const int lane = threadIdx.x & 63;
+    s[0] = s[1] = s[2] = 0.0;
+#pragma unroll
+    for (int q0 = 0; q0 < PER; q0 += CH) {
+        double2 c[CH], up[CH], dn[CH], fv[CH];
+        double lf[CH], rt[CH];
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            const int j = 2 * (lane + 64 * (q0 + q));
+            c[q] = ld2(u + j);
+            up[q] = ld2(u + j - pitch);
+            dn[q] = ld2(u + j + pitch);
+            fv[q] = ld2(f + j);
+            lf[q] = u[max(j - 1, 0)];
+            rt[q] = u[j + 2];
+        }
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            const int j = 2 * (lane + 64 * (q0 + q));
+            const double in = j > 0 ? 1.0 : 0.0;  // node 0 is a boundary node
+            const double r0 = in * (fv[q].x - (lf[q] + c[q].y + up[q].x + dn[q].x - 4.0 * c[q].x) * ih2);
+            const double r1 = fv[q].y - (c[q].x + rt[q] + up[q].y + dn[q].y - 4.0 * c[q].y) * ih2;
+            V[pidx(j)] = r0;
+            V[pidx(j + 1)] = r1;
+            s[0] += r0 * r0 + r1 * r1;
+            s[1] += in * fv[q].x * fv[q].x + fv[q].y * fv[q].y;
+            s[2] += in * c[q].x * c[q].x + c[q].y * c[q].y;
+        }
+    }
+}
 
 // Twiddle W_L^m (m < L) from the table of W_L^m, m < L / 2 (W_L^(m + L/2) = -W_L^m).
 template <int L>
@@ -240,7 +290,11 @@ __device__ __forceinline__ void wdst(const Get& get, const double (&sn)[FstSize<
 // last row transforms the last row again and writes nothing.  With RW > 1 the
 // transposed writes of MODE 0 and 1 go through LDS, RW consecutive rows'
 // values of one coefficient written together.
-template <typename E, int LOGN, int MODE, int RW>
+// TOP (E = double): the level is the finest one and the pass belongs to a
+// whole Poisson solve: the x pass transforms the residual f - L_h u of the
+// incoming iterate, formed row by row in LDS, and records its norms; the
+// inverse x pass adds the correction to u.
+template <typename E, int LOGN, int MODE, int RW, bool TOP>
 __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
     using F = FstSize<LOGN>;
     constexpr int n = F::n, H = F::H, NB = F::NB, PER = F::PER, LP = F::LP;
@@ -279,7 +333,21 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
     }
     const size_t ld = a.ld;
     double xe[PER], xo[PER];
-    if (MODE == 0) {
+    if constexpr (MODE == 0 && TOP) {
+        double* V = buf;
+        double s[3];
+        residual_row<PER>(a.u[r] + (size_t)(p + 1) * a.pitch, a.f[r] + (size_t)(p + 1) * a.pitch,
+                          a.pitch, a.ih2, V, s);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], d, 64);
+        if (lane < 3 && live)
+            a.norm_part[(size_t)(3 * r + lane) * a.nblk + p] = lane == 0 ? s[0] : lane == 1 ? s[1] : s[2];
+        wave_sync();
+        const auto get = [=](int j) { return V[pidx(j)]; };
+        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+    } else if (MODE == 0) {
         const E* row = a.f[r] + (size_t)(p + 1) * a.pitch;
         const auto get = [=](int j) { return (double)row[j]; };
         wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
@@ -296,11 +364,11 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int k = lane * PER + q;
-            V[2 * k] = k == 0 ? 0.0 : xe[q] / (lk + lam * s2e[q]);
-            V[2 * k + 1] = xo[q] / (lk + lam * s2o[q]);
+            V[pidx(2 * k)] = k == 0 ? 0.0 : xe[q] / (lk + lam * s2e[q]);
+            V[pidx(2 * k + 1)] = xo[q] / (lk + lam * s2o[q]);
         }
         wave_sync();
-        const auto get = [=](int j) { return V[j]; };
+        const auto get = [=](int j) { return V[pidx(j)]; };
         wdst<LOGN, false>(get, sn, buf, T, tv, xe, xo);
     }
     if (MODE < 2 && RW == 1) {
@@ -317,14 +385,36 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int k = lane * PER + q;
-            buf[2 * k] = xe[q];
-            buf[2 * k + 1] = xo[q];
+            buf[pidx(2 * k)] = xe[q];
+            buf[pidx(2 * k + 1)] = xo[q];
         }
         __syncthreads();
         double* Tt = (MODE == 0 ? a.t1 : a.t2)[r] + pb * RW;
         for (int i = threadIdx.x; i < (n - 1) * RW; i += 64 * RW) {
             const int c = 1 + i / RW, ww = i % RW;
-            if (pb * RW + ww < n - 1) Tt[(size_t)(c - 1) * ld + ww] = bufs[ww][c];
+            if (pb * RW + ww < n - 1) Tt[(size_t)(c - 1) * ld + ww] = bufs[ww][pidx(c)];
+        }
+    } else if constexpr (TOP) {
+        // u += scale X through LDS: coalesced pairs, as residual_row
+        double* V = buf;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int k = lane * PER + q;
+            V[pidx(2 * k)] = k == 0 ? 0.0 : xe[q];
+            V[pidx(2 * k + 1)] = xo[q];
+        }
+        wave_sync();
+        const double sc = a.scale;
+        double* row = a.u[r] + (size_t)(p + 1) * a.pitch;
+        double2 uv[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) uv[q] = ld2(row + 2 * (lane + 64 * q));
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int j = 2 * (lane + 64 * q);
+            uv[q].x += sc * V[pidx(j)];
+            uv[q].y += sc * V[pidx(j + 1)];
+            *reinterpret_cast<double2*>(row + j) = uv[q];
         }
     } else {
         E* u = a.u[r];
@@ -352,7 +442,7 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
 #define WQ_FST_ROWS 2
 #endif
 
-template <typename E, int LOGN>
+template <typename E, int LOGN, bool TOP>
 void launch_fst(wandqs_ctx* c, const FstArgs<E>& a, int R, const char* tname) {
     constexpr int n = 1 << LOGN;
     constexpr int RW = LOGN <= 10 ? WQ_FST_ROWS : 1;
@@ -362,18 +452,18 @@ void launch_fst(wandqs_ctx* c, const FstArgs<E>& a, int R, const char* tname) {
     char nm[64];
     {
         std::snprintf(nm, sizeof nm, "k_fst<%s, x>@%d", tname, n);
-        ProfScope ps(c, nm, nodes * (eb + 8.0));
-        WQ_KLAUNCH(ps, (k_fst<E, LOGN, 0, RW>), gw, dim3(64 * RW), 0, c->stream, a);
+        ProfScope ps(c, nm, nodes * (eb + 8.0 + (TOP ? 8.0 : 0.0)));
+        WQ_KLAUNCH(ps, (k_fst<E, LOGN, 0, RW, TOP>), gw, dim3(64 * RW), 0, c->stream, a);
     }
     {
         std::snprintf(nm, sizeof nm, "k_fst<%s, y>@%d", tname, n);
         ProfScope ps(c, nm, nodes * 16.0);
-        WQ_KLAUNCH(ps, (k_fst<E, LOGN, 1, RW>), gw, dim3(64 * RW), 0, c->stream, a);
+        WQ_KLAUNCH(ps, (k_fst<E, LOGN, 1, RW, TOP>), gw, dim3(64 * RW), 0, c->stream, a);
     }
     {
         std::snprintf(nm, sizeof nm, "k_fst<%s, xinv>@%d", tname, n);
-        ProfScope ps(c, nm, nodes * (8.0 + eb));
-        WQ_KLAUNCH(ps, (k_fst<E, LOGN, 2, 1>), g, dim3(64), 0, c->stream, a);
+        ProfScope ps(c, nm, nodes * (8.0 + eb + (TOP ? 8.0 : 0.0)));
+        WQ_KLAUNCH(ps, (k_fst<E, LOGN, 2, 1, TOP>), g, dim3(64), 0, c->stream, a);
     }
 }
 
@@ -398,13 +488,45 @@ bool fst_used(const wandqs_ctx* c) {
 
 size_t fst_ld(const wandqs_ctx* c) { return (size_t)c->lev[1].N + 8; }
 
+bool fst_top_used(const wandqs_ctx* c) { return c->N >= kFstMinN && c->N <= kFstMaxN; }
+
 wandqs_status make_fst_tables(wandqs_ctx* c) {
-    if (!fst_used(c)) return WANDQS_OK;
-    const int L = 2 * c->lev[1].N;
-    hipLaunchKernelGGL(k_fst_tables, dim3(L / 256 + 1), dim3(256), 0, c->stream, L, c->fst_tw,
-                       c->fst_s2);
+    const auto make = [c](int n, double2* tw, double* s2) {
+        const int L = 2 * n;
+        hipLaunchKernelGGL(k_fst_tables, dim3(L / 256 + 1), dim3(256), 0, c->stream, L, tw, s2);
+    };
+    if (fst_used(c)) make(c->lev[1].N, c->fst_tw, c->fst_s2);
+    if (c->fst_top_tw) make(c->N, c->fst_top_tw, c->fst_top_s2);
     WQ_LAUNCH_CHECK();
     return WANDQS_OK;
+}
+
+void fst_top_iteration(wandqs_ctx* c, int R, const double* const* f, double* const* u,
+                       double* norm_part) {
+    const Level& L0 = c->lev[0];
+    FstArgs<double> a{};
+    a.pitch = L0.pitch;
+    a.ld = L0.N + 8;
+    for (int r = 0; r < R; ++r) {
+        a.f[r] = f[r];
+        a.u[r] = u[r];
+        a.t1[r] = c->fst_t1[r];
+        a.t2[r] = c->fst_t2[r];
+    }
+    a.tw = c->fst_top_tw;
+    a.s2 = c->fst_top_s2;
+    a.lam = -4.0 / (L0.h * L0.h);
+    a.scale = (2.0 / L0.N) * (2.0 / L0.N);
+    a.ih2 = 1.0 / (L0.h * L0.h);
+    a.norm_part = norm_part;
+    a.nblk = L0.N - 1;
+    switch (L0.N) {
+        case 128: launch_fst<double, 7, true>(c, a, R, "top"); break;
+        case 256: launch_fst<double, 8, true>(c, a, R, "top"); break;
+        case 512: launch_fst<double, 9, true>(c, a, R, "top"); break;
+        case 1024: launch_fst<double, 10, true>(c, a, R, "top"); break;
+        default: launch_fst<double, 11, true>(c, a, R, "top"); break;
+    }
 }
 
 template <typename E>
@@ -425,11 +547,11 @@ void fst_solve(wandqs_ctx* c, int R, const E* const* f, E* const* u) {
     a.scale = (2.0 / L1.N) * (2.0 / L1.N);
     const char* tn = sizeof(E) == 8 ? "double" : "float";
     switch (L1.N) {
-        case 128: launch_fst<E, 7>(c, a, R, tn); break;
-        case 256: launch_fst<E, 8>(c, a, R, tn); break;
-        case 512: launch_fst<E, 9>(c, a, R, tn); break;
-        case 1024: launch_fst<E, 10>(c, a, R, tn); break;
-        default: launch_fst<E, 11>(c, a, R, tn); break;
+        case 128: launch_fst<E, 7, false>(c, a, R, tn); break;
+        case 256: launch_fst<E, 8, false>(c, a, R, tn); break;
+        case 512: launch_fst<E, 9, false>(c, a, R, tn); break;
+        case 1024: launch_fst<E, 10, false>(c, a, R, tn); break;
+        default: launch_fst<E, 11, false>(c, a, R, tn); break;
     }
 }
 

@@ -1720,52 +1720,67 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_k2(int N, int pitch, 
     }
 }
 
-// Residual norms of the current iterate over the same tiles as the down pass.
-// With r_out set (mixed form), the FP64 residual is also stored, rounded to
-// float, as the right-hand side of the FP32 error equation (boundary 0).
-template <int R, bool HELM>
-__global__ __launch_bounds__(kThreads) void k_resnorm(int N, double h, int pitch,
-                                                      const double* u0, const double* u1,
-                                                      const double* f0, const double* f1,
-                                                      const double* k2, double* part, int nblk,
-                                                      float* r0, float* r1, int pitch32, int TX,
-                                                      int TY) {
-    __shared__ double red[(kThreads / 64) * 3 * R];
-    const double ih2 = 1.0 / (h * h);
-    const int x0 = blockIdx.x * TX, y0 = blockIdx.y * TY;
-    const double* u[2] = {u0, u1};
-    const double* f[2] = {f0, f1};
-    float* ro[2] = {r0, r1};
-    double acc[3 * R];
+// Residual norms of the current iterate, one partial sum per interior row and
+// right-hand side (one wavefront a row, four rows a workgroup; blockIdx.y the
+// right-hand side).  With r_out set (mixed form), the FP64 residual is also
+// stored, rounded to float, as the right-hand side of the FP32 error equation
+// (boundary 0).  HBM-bound on the large grids: the loads of four node pairs a
+// lane are in flight together (one node a thread and trip, a branch around
+// each, measured 10.9 us for two right-hand sides at 512^2).
+template <bool HELM>
+__global__ __launch_bounds__(kThreads) void k_resnorm(int N, double ih2, int pitch, const double* u0,
+                                                      const double* u1, const double* f0,
+                                                      const double* f1, const double* k2,
+                                                      double* part, int nblk, float* r0, float* r1) {
+    constexpr int CH = 4;
+    int bx, r;
+    tile_of_block(bx, r);
+    const int lane = threadIdx.x & 63, row = bx * (kThreads / 64) + (threadIdx.x >> 6) + 1;
+    if (row > N - 1) return;
+    const size_t g0 = (size_t)row * pitch;
+    const double* u = (r ? u1 : u0) + g0;
+    const double* f = (r ? f1 : f0) + g0;
+    float* ro = r ? r1 : r0;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int m0 = 0; m0 < N / 2; m0 += 64 * CH) {
+        double2 c[CH], up[CH], dn[CH], fv[CH], kv[CH];
+        double lf[CH], rt[CH];
 #pragma unroll
-    for (int k = 0; k < 3 * R; ++k) acc[k] = 0.0;
-    for (int i = threadIdx.x; i < TX * TY; i += kThreads) {
-        const int oy = i / TX, ox = i - oy * TX;
-        const int gx = x0 + ox, gy = y0 + oy;
-        if (gx > N - 1 || gy > N - 1) continue;
-        const bool interior = gx >= 1 && gy >= 1;
-        const size_t g = (size_t)gy * pitch + gx;
+        for (int q = 0; q < CH; ++q) {
+            const int j = 2 * min(m0 + lane + 64 * q, N / 2 - 1);
+            c[q] = *reinterpret_cast<const double2*>(u + j);
+            up[q] = *reinterpret_cast<const double2*>(u + j - pitch);
+            dn[q] = *reinterpret_cast<const double2*>(u + j + pitch);
+            fv[q] = *reinterpret_cast<const double2*>(f + j);
+            if (HELM) kv[q] = *reinterpret_cast<const double2*>(k2 + g0 + j);
+            lf[q] = u[max(j - 1, 0)];
+            rt[q] = u[j + 2];
+        }
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            double rr = 0.0;
-            if (interior) {
-                const double* q = u[r];
-                double au = (q[g - 1] + q[g + 1] + q[g - pitch] + q[g + pitch] - 4.0 * q[g]) * ih2;
-                if (HELM) au -= k2[g] * q[g];
-                rr = f[r][g] - au;
-                acc[3 * r] += rr * rr;
-                acc[3 * r + 1] += f[r][g] * f[r][g];
-                acc[3 * r + 2] += q[g] * q[g];
+        for (int q = 0; q < CH; ++q) {
+            const int j = 2 * (m0 + lane + 64 * q);
+            if (j >= N) continue;
+            const bool in = j > 0;  // node 0 is a boundary node
+            double a0 = (lf[q] + c[q].y + up[q].x + dn[q].x - 4.0 * c[q].x) * ih2;
+            double a1 = (c[q].x + rt[q] + up[q].y + dn[q].y - 4.0 * c[q].y) * ih2;
+            if (HELM) {
+                a0 -= kv[q].x * c[q].x;
+                a1 -= kv[q].y * c[q].y;
             }
-            if (ro[0]) ro[r][(size_t)gy * pitch32 + gx] = (float)rr;
+            const double v0 = in ? fv[q].x - a0 : 0.0, v1 = fv[q].y - a1;
+            const double w = in ? 1.0 : 0.0;
+            s[0] += v0 * v0 + v1 * v1;
+            s[1] += w * fv[q].x * fv[q].x + fv[q].y * fv[q].y;
+            s[2] += w * c[q].x * c[q].x + c[q].y * c[q].y;
+            if (ro) *reinterpret_cast<float2*>(ro + g0 + j) = float2{(float)v0, (float)v1};
         }
     }
-    block_sum<3 * R, kThreads>(acc, red);
-    if (threadIdx.x == 0) {
-        const int b = blockIdx.y * gridDim.x + blockIdx.x;
 #pragma unroll
-        for (int k = 0; k < 3 * R; ++k) part[k * nblk + b] = acc[k];
-    }
+    for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], d, 64);
+    if (lane < 3)
+        part[(size_t)(3 * r + lane) * nblk + row - 1] = lane == 0 ? s[0] : lane == 1 ? s[1] : s[2];
 }
 
 // Mixed form: u += e on the interior nodes (the FP32 correction added in FP64).
@@ -2225,33 +2240,26 @@ void vcycle(wandqs_ctx* c, int R, bool helm, const Hier<E>& hz, bool zero_guess,
     }
 }
 
-// FP64 residual norms of the level-0 iterate into `slot`; with r32 set the
-// residual is also stored in float (the mixed form's defect).
+// FP64 residual norms of the level-0 iterate into `slot` (one partial per
+// interior row); with r32 set the residual is also stored in float (the mixed
+// form's defect).
 void resnorm(wandqs_ctx* c, int R, bool helm, const Hier<double>& hz, int slot,
              float* const* r32) {
     const wq::Level& L = c->lev[0];
-    // the same tiles as the level-0 down pass: every norm slot of a solve has
-    // one partial-sum layout
-    const PassGeom pg = pass_geom(c, L.N, nu_pre_at(c, 0), true);
-    const dim3 g = pg.grid;
-    const int TX = pg.TX, TY = pg.TY;
+    const dim3 g((L.N - 1 + kThreads / 64 - 1) / (kThreads / 64), R);
     double* part = c->norm_part + (size_t)slot * kNormVec * c->max_tiles;
-    const int nblk = g.x * g.y;
-    const double* u1 = R > 1 ? hz.u0[1] : nullptr;
-    const double* f1 = R > 1 ? hz.f0[1] : nullptr;
+    const double ih2 = 1.0 / (L.h * L.h);
     float* o0 = r32 ? r32[0] : nullptr;
     float* o1 = (r32 && R > 1) ? r32[1] : nullptr;
     char nm[56];
-    prof_name(c, nm, sizeof nm, "k_resnorm<%d, %s>%s", R, helm ? "true" : "false",
-                  r32 ? "+defect" : "");
+    prof_name(c, nm, sizeof nm, "k_resnorm<%s>%s", helm ? "true" : "false", r32 ? "+defect" : "");
     ProfScope ps(c, nm, (double)L.N * L.N * (16.0 * R + (helm ? 8.0 : 0.0) + (r32 ? 4.0 * R : 0.0)));
-    if (R == 1) {
-        if (helm) WQ_KLAUNCH(ps, (k_resnorm<1, true>), g, dim3(kThreads), 0, c->stream, L.N, L.h, L.pitch, hz.u0[0], u1, hz.f0[0], f1, hz.k2, part, nblk, o0, o1, L.pitch, TX, TY);
-        else WQ_KLAUNCH(ps, (k_resnorm<1, false>), g, dim3(kThreads), 0, c->stream, L.N, L.h, L.pitch, hz.u0[0], u1, hz.f0[0], f1, hz.k2, part, nblk, o0, o1, L.pitch, TX, TY);
-    } else {
-        if (helm) WQ_KLAUNCH(ps, (k_resnorm<2, true>), g, dim3(kThreads), 0, c->stream, L.N, L.h, L.pitch, hz.u0[0], u1, hz.f0[0], f1, hz.k2, part, nblk, o0, o1, L.pitch, TX, TY);
-        else WQ_KLAUNCH(ps, (k_resnorm<2, false>), g, dim3(kThreads), 0, c->stream, L.N, L.h, L.pitch, hz.u0[0], u1, hz.f0[0], f1, hz.k2, part, nblk, o0, o1, L.pitch, TX, TY);
-    }
+    if (helm)
+        WQ_KLAUNCH(ps, k_resnorm<true>, g, dim3(kThreads), 0, c->stream, L.N, ih2, L.pitch, hz.u0[0],
+                   hz.u0[1], hz.f0[0], hz.f0[1], hz.k2, part, L.N - 1, o0, o1);
+    else
+        WQ_KLAUNCH(ps, k_resnorm<false>, g, dim3(kThreads), 0, c->stream, L.N, ih2, L.pitch, hz.u0[0],
+                   hz.u0[1], hz.f0[0], hz.f0[1], hz.k2, part, L.N - 1, o0, o1);
 }
 
 // One outer iteration of the mixed form: defect r = f - A u in FP64 (stored in
@@ -2347,6 +2355,25 @@ wandqs_status wait_published(wandqs_ctx* c, const uint32_t* h_seq, uint32_t seq)
     return WANDQS_E_HIP;
 }
 
+// Poisson solves in tolerance mode on grids of 128^2 .. 2048^2 iterate
+// u += L_h^-1 (f - L_h u) with the exact sine-transform solve on the finest
+// level itself (fst.hip) in FP64, in both precision forms: the correction's
+// rounding (1e-14 .. 3e-13 of it) is the only error an iteration leaves, so from
+// an extrapolated guess one iteration reaches the rounding floor and from zero
+// two do, where the V-cycles that end with the same solve one level down took 5
+// to 7.  The three
+// solves of a slice at 1024^2: 130 instead of 446 us (kernel time), at 256^2
+// 46 instead of 310 us.
+// A caller that allows fewer than kDirectMinCycles cycles counts V-cycles (and
+// may want the WANDQS_E_NOCONV they end with), so it keeps them; with that many
+// the V-cycles (a factor 10 and more per cycle) converge as well.  Fixed mode
+// (mg_rtol <= 0) is a number of V-cycles by definition.
+constexpr int kDirectMinCycles = 16;
+bool direct_poisson(const wandqs_ctx* c, bool helm) {
+    return !helm && c->cfg.mg_rtol > 0.0 && c->cfg.mg_max_cycles >= kDirectMinCycles &&
+           c->fst_top_tw != nullptr;
+}
+
 // Solve with the context's stop rule.  Tolerance mode (mg_rtol > 0) runs a batch
 // of V-cycles sized by the previous slice's count for this solve, reads the
 // residual norms back once per batch and adds single cycles until every
@@ -2386,6 +2413,7 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     hipStream_t s = c->stream;
     Hier<double> hz{{u[0], R > 1 ? u[1] : nullptr}, {f[0], R > 1 ? f[1] : nullptr}, k2};
     const bool mixed = c->cfg.precision == WANDQS_MIXED;
+    const bool direct = direct_poisson(c, helm);
     if (helm && !k2_levels_ready) {
         const wandqs_status st = helm_levels(c, k2);
         if (st != WANDQS_OK) return st;
@@ -2396,11 +2424,14 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     // upslot >= 0 (FP64, register tiles on level 0): the cycle's finest up pass
     // records the norms of its result in slot upslot
     auto cycle = [&](int slot, int upslot, const FuseCtl& fz) {
-        const int fk = (fz.skip_down0 ? 1 : 0) | (fz.fuse_up0 ? 2 : 0) | (fz.cur ? 4 : 0);
+        const int fk = (fz.skip_down0 ? 1 : 0) | (fz.fuse_up0 ? 2 : 0) | (fz.cur ? 4 : 0) |
+                       (direct ? 8 : 0);
         const CycleKey key{{hz.u0[0], hz.u0[1], hz.f0[0], hz.f0[1], hz.k2}, R, helm, mixed, slot,
                            upslot, fk};
         const hipError_t e = run_cycle(c, key, [&] {
-            if (mixed) mixed_iteration(c, R, helm, hz, slot);
+            if (direct)
+                fst_top_iteration(c, R, hz.f0, hz.u0, c->norm_part + (size_t)slot * kNormVec * c->max_tiles);
+            else if (mixed) mixed_iteration(c, R, helm, hz, slot);
             else vcycle<double>(c, R, helm, hz, false, slot, upslot, nullptr, &fz);
         });
         if (gerr == hipSuccess) gerr = e;
@@ -2423,15 +2454,16 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     }
     const int N = c->N;
     const double atol = c->cfg.mg_atol * std::sqrt((double)(N - 1) * (N - 1));
-    // partial sums per tile (the level-0 tiles, for both the down pass and the
-    // residual-norm kernel)
+    // partial sums of the norms per slot
+    // (the V-cycles' down passes: one per level-0 tile; resnorm and the sine
+    // transform solve: one per interior row)
     const dim3 g = pass_geom(c, N, nu_pre_at(c, 0), true).grid;
-    const int nblk = g.x * g.y;
+    const int nblk = mixed || direct || separate_norm ? N - 1 : g.x * g.y;
     // the batch's last cycle records the final norms in its finest up pass
     // (register tiles, FP64) instead of a separate residual pass
     const PassGeom gu = pass_geom(c, N, c->cfg.nu_post, false, true);
-    const bool up_norms = !mixed && !separate_norm && gu.reg;
-    const int nblk_up = gu.grid.x * gu.grid.y;
+    const bool up_norms = !mixed && !direct && !separate_norm && gu.reg;
+    const int nblk_up = up_norms ? (int)(gu.grid.x * gu.grid.y) : N - 1;
     // inside a batch, each cycle's level-0 up pass but the last fuses with the
     // next cycle's down pass; their norm slots have the fused launch's tiles
     const bool fuse = !mixed && up_norms && fuse_possible(c);
@@ -2470,8 +2502,7 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
         {
             ProfScope ps(c, "k_reduce_publish", 8.0 * ns * 3 * R * (nblk + 1));
             WQ_KLAUNCH(ps, k_reduce_publish, dim3(ns * 3 * R), dim3(kThreads), 0, s,
-                       c->norm_part, V * c->max_tiles, nblk, s0, 3 * R, up_norms ? done + b : -1,
-                       nblk_up, fuse ? done + 1 : 0, fuse ? done + b : 0, nblk_fuse, hr, c->flags,
+                       c->norm_part, V * c->max_tiles, nblk, s0, 3 * R, done + b, nblk_up, fuse ? done + 1 : 0, fuse ? done + b : 0, nblk_fuse, hr, c->flags,
                        h_flags, h_seq, seq, c->pub_count);
         }
         WQ_LAUNCH_CHECK();

@@ -305,6 +305,11 @@ struct wandqs_ctx {
     double* fst_t2[2] = {};
     double2* fst_tw = nullptr;
     double* fst_s2 = nullptr;
+    // the same tables for the whole Poisson solve on the finest level (grids of
+    // 128^2 .. 2048^2; null where none is made), whose intermediates share
+    // fst_t1, fst_t2 ([N - 1][N + 8] then)
+    double2* fst_top_tw = nullptr;
+    double* fst_top_s2 = nullptr;
     double* pa[2][4] = {};
     int32_t* pid[2] = {};
     int cur = 0;
@@ -380,6 +385,11 @@ size_t fst_ld(const wandqs_ctx* c);
 wandqs_status make_fst_tables(wandqs_ctx* c);
 template <typename E>
 void fst_solve(wandqs_ctx* c, int R, const E* const* f, E* const* u);
+// one iteration u += L_h^-1 (f - L_h u) on the finest level; the norms of the
+// incoming iterate go to norm_part, one entry per interior row
+bool fst_top_used(const wandqs_ctx* c);
+void fst_top_iteration(wandqs_ctx* c, int R, const double* const* f, double* const* u,
+                       double* norm_part);
 
 // multigrid (mg.hip)
 // ahead (optional): work that reads the solution but does not change what the
