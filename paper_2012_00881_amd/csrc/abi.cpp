@@ -346,6 +346,20 @@ wandqs_status check_flags(wandqs_ctx* c) {
     return WANDQS_OK;
 }
 
+// Tables of the coarse Helmholtz levels.
+template <class Take>
+void carve_ctab(wandqs_ctx* c, Take&& take) {
+    using wq::kCoarseTab;
+    using wq::kCoarseTop;
+    wq::CoarseTabs& t = c->ctab;
+    double** d[4] = {&t.D, &t.id, &t.TD, &t.Tid};
+    float** f[4] = {&t.Df, &t.idf, &t.TDf, &t.Tidf};
+    for (int k = 0; k < 4; ++k) {
+        *d[k] = (double*)take(sizeof(double) * (k < 2 ? kCoarseTop : kCoarseTab));
+        *f[k] = (float*)take(sizeof(float) * (k < 2 ? kCoarseTop : kCoarseTab));
+    }
+}
+
 // Tables of the exact coarse Poisson solves (the 64^2 sine matrices in float,
 // with double copies for the mixed form's FP64 coarsest-grid solve) and the
 // arrays of the fast sine transform solves on level 1 and (top) on the finest
@@ -403,13 +417,7 @@ size_t wq::carve(wandqs_ctx* c, char* base) {
     L0.k2 = arr(0);
     for (int k = 0; k < 6; ++k) c->mom[k] = arr(0);
     c->jz = arr(0);
-    {
-        int tot = 0;
-        for (int n = c->lev[c->lc].N; n >= 2; n /= 2) tot += (n + 1) * (n + 1);
-        c->k2lev = (double*)take(sizeof(double) * (size_t)tot);
-        c->k2levf = (float*)take(sizeof(float) * (size_t)tot);
-        c->idlevf = (float*)take(sizeof(float) * (size_t)tot);
-    }
+    carve_ctab(c, take);
     carve_dst(c, take, true);
     for (int l = 1; l <= c->lc; ++l) {
         Level& L = c->lev[l];
@@ -552,13 +560,7 @@ size_t wq::carve_solver(wandqs_ctx* c, char* base) {
         L0.f[r] = arr(0);
     }
     L0.k2 = arr(0);
-    {
-        int tot = 0;
-        for (int n = c->lev[c->lc].N; n >= 2; n /= 2) tot += (n + 1) * (n + 1);
-        c->k2lev = (double*)take(sizeof(double) * (size_t)tot);
-        c->k2levf = (float*)take(sizeof(float) * (size_t)tot);
-        c->idlevf = (float*)take(sizeof(float) * (size_t)tot);
-    }
+    carve_ctab(c, take);
     carve_dst(c, take, false);
     for (int l = 1; l <= c->lc; ++l) {
         Level& L = c->lev[l];

@@ -36,12 +36,6 @@ void prof_name(const wandqs_ctx* c, char* nm, size_t n, const char* fmt, A... a)
     else nm[0] = 0;
 }
 
-#ifndef WQ_COARSE_CYCLES
-#define WQ_COARSE_CYCLES 1
-#endif
-#ifndef WQ_COARSE_F32
-#define WQ_COARSE_F32 1
-#endif
 #ifndef WQ_SMALL_TILE_MAX
 #define WQ_SMALL_TILE_MAX 256
 #endif
@@ -55,10 +49,6 @@ constexpr double kOmegaH2N0 = 0.125;
 // second sweep there cost more time than the extra V-cycles it saved
 // (measured).  The finer levels and every post-smoothing keep nu_pre, nu_post.
 constexpr int kFullPreLevels = 2;
-#ifndef WQ_COARSE_THREADS
-#define WQ_COARSE_THREADS 1024
-#endif
-constexpr int kCoarseThreads = WQ_COARSE_THREADS;
 // Tile kernels: 32 x 32 owned nodes with 512 threads, or 16 x 16 with 256
 // threads on the levels N <= WQ_SMALL_TILE_MAX (more workgroups and a shorter
 // chain of dependent LDS phases per workgroup where the grid is small).
@@ -1103,340 +1093,453 @@ __global__ __launch_bounds__(64 * NW) void k_mg_updown_reg(FuseArgs<E> a) {
 
 
 // ---------------------------------------------------------------- coarse --
+//
+// The levels of at most 64^2 cells of the Helmholtz V-cycle, and whole solves on
+// grids that small, in one workgroup per right-hand side with the iterate in
+// registers.  The 64^2 level lies across kCoarseWaves wavefronts (lane = column,
+// 64 / kCoarseWaves rows each); the levels below run in the first wavefront
+// alone, 64 / n row groups side by side, with no workgroup barrier.  The grid's
+// boundary column and row 0 lie in the layout and are held at 0 by a zero 1/D;
+// those at n read as 0 past the end.
+//
+// A lane's rows come in pairs (2m, 2m + 1), one red node ((x + y) even) and one
+// black each, held as two arrays: with p = x mod 2 the red node of pair m lies
+// in row 2m + p, the black one in row 2m + 1 - p.  A node's left and right
+// neighbours are then the other colour's entry m of the neighbouring lanes (DPP
+// wave shifts), its vertical ones the lane's own entry m and m + 1 or m - 1:
+// every half sweep updates one node per lane and pair, with no divergence and
+// no LDS but the row that crosses to the next wavefront or group.
+//
+// What bounds it is the serial chain of half sweeps and transfers of one
+// workgroup per right-hand side, and its loads: 11.6 us per V-cycle and launch in
+// float, 15.4 in double, about 6 for each further cycle of a launch (every level
+// in LDS with a workgroup barrier per half sweep and one cycle per launch: 22.2
+// and 28.3).  Four wavefronts: with eight the double form spills (19.7 us, float
+// 12.1).
+constexpr int kCoarseWaves = 4;
+static_assert(kCoarseMax == 64, "the coarse kernel holds levels up to 64 cells a side");
+
+// Level of n <= 32 cells in one wavefront: G groups of ROWS rows, NP row pairs
+// per lane (lanes past G n idle).  Offsets of its LDS arrays: E, the correction
+// it hands to the next finer level ((n + 1)^2); F, its right-hand side (n^2);
+// T, its 1/D and D in the lane layout (entry (2 m + colour) 64 + lane).
+template <int n>
+struct CoarseLevel {
+    static constexpr int G = n >= 16 ? 64 / n : (n == 8 ? 4 : 2);
+    static constexpr int ROWS = n / G, NP = ROWS / 2;
+};
+template <int n0>
+constexpr int coarse_threads() { return n0 == 64 ? 64 * kCoarseWaves : 64; }
+template <int n0>
+constexpr int coarse_rows() {
+    if constexpr (n0 == 64) return 64 / kCoarseWaves;
+    else return CoarseLevel<n0>::ROWS;
+}
+constexpr int coarse_off_E(int n) {  // levels 32, 16, 8, 4, 2
+    int o = 0;
+    for (int k = 32; k > n; k /= 2) o += (k + 1) * (k + 1);
+    return o;
+}
+constexpr int coarse_off_F(int n) {
+    int o = 0;
+    for (int k = 32; k > n; k /= 2) o += k * k;
+    return o;
+}
+constexpr int coarse_off_T(int n) {  // levels 32, 16, 8, 4: NP = 8, 2, 1, 1
+    return n == 32 ? 0 : n == 16 ? 1024 : n == 8 ? 1280 : n == 4 ? 1408 : 1536;
+}
+
+constexpr int kCoarseT = coarse_off_T(2);
+static_assert(kCoarseT < kCoarseTab, "room for the tables");
+
+// The node of an entry of the T tables: its level, row and column, and whether
+// it is an interior one (the rest: boundary, idle lanes).
+struct CoarseSlot {
+    int n, x, y;
+    bool in;
+};
+__device__ __forceinline__ CoarseSlot coarse_slot(int i) {
+    const int n = i >= coarse_off_T(4) ? 4 : i >= coarse_off_T(8) ? 8 : i >= coarse_off_T(16) ? 16 : 32;
+    const int rows = n == 32 ? 16 : n == 16 ? 4 : 2, groups = n == 32 ? 2 : n == 4 ? 2 : 4;
+    const int e = i - (n == 32 ? 0 : n == 16 ? coarse_off_T(16) : n == 8 ? coarse_off_T(8) : coarse_off_T(4));
+    const int lane = e & 63, m = e >> 7, colour = (e >> 6) & 1;
+    CoarseSlot c;
+    c.n = n;
+    c.x = lane & (n - 1);
+    const int g = lane / n;
+    c.y = g * rows + 2 * m + ((lane & 1) ^ colour);
+    c.in = g < groups && c.x > 0 && c.y > 0;
+    return c;
+}
+
+template <typename C>
+struct CoarseLds {
+    C E[coarse_off_E(1)];
+    C F[coarse_off_F(1)];
+    C id[kCoarseT], D[kCoarseT];
+    C edge[2][kCoarseWaves + 2][64];  // rows across the wavefronts of the 64^2 level
+    double red[kCoarseWaves][3];
+};
 
 template <typename E>
 struct CoarseArgs {
-    int N;  // <= kCoarseMax
-    double h;
+    double h;  // of the top level
     int pitch;
     const E* f[2];
-    const E* u_init[2];   // nullptr: zero initial guess
-    const double* k2lev;  // Helmholtz: k2 of every level N..2, dense, concatenated
-    const float* k2levf;  // the same in float, and 1 / (4 + h_l^2 k2) in float
-    const float* idlevf;
+    const E* u_init[2];  // nullptr: zero initial guess
+    CoarseTabs tab;  // Helmholtz: what k_coarse_k2 made of k2
     E* u_out[2];
-    int ncycles, nu1, nu2;
-    double omega;   // relaxation factor of the levels with h^2 <= h2max (Helmholtz)
-    double h2max;   // coarser Helmholtz levels relax with factor 1
+    int ncycles, inner;  // ncycles times inner V-cycles
+    int nu1, nu2;
+    double omega;       // relaxation factor of the levels with h^2 <= h2max (Helmholtz)
+    double h2max;       // coarser Helmholtz levels relax with factor 1
+    double* norm_part;  // nullptr, or the sums of r^2, f^2, u^2 before each of the ncycles and after
+    size_t norm_stride;  // the last ([3 r + q] of slots norm_stride apart)
 };
 
-constexpr int coarse_nodes() {
-    int t = 0;
-    for (int n = kCoarseMax; n >= 2; n /= 2) t += (n + 1) * (n + 1);
-    return t;
+// the tables in the type of the sweeps
+template <typename C> __device__ __forceinline__ const C* coarse_tab(const double* d, const float* f);
+template <> __device__ __forceinline__ const double* coarse_tab<double>(const double* d, const float*) { return d; }
+template <> __device__ __forceinline__ const float* coarse_tab<float>(const double*, const float* f) { return f; }
+
+// One half sweep: the nodes s (sor_update) from the other colour o.  q: the
+// node's second vertical neighbour is entry m + 1, else m - 1; e: that of the
+// lane's last or first pair, from the next wavefront or group.
+template <typename C, int NP>
+__device__ __forceinline__ void coarse_half(C (&s)[NP], const C (&f)[NP], const C (&id)[NP],
+                                            const C (&o)[NP], C e, bool q, C h2, C om) {
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+        const C hi = m + 1 < NP ? o[m + 1 < NP ? m + 1 : m] : e, lo = m > 0 ? o[m > 0 ? m - 1 : 0] : e;
+        const C nb = lane_shift<kFromLeft>(o[m]) + lane_shift<kFromRight>(o[m]) + o[m] + (q ? hi : lo);
+        s[m] = sor_update(s[m], nb, f[m], id[m], h2, om);
+    }
 }
 
-// Levels of at most WQ_COARSE_WAVE_N cells a side run in the first wavefront
-// alone: a phase there has a few dozen nodes, and ordering its LDS traffic
-// inside one wavefront (whose LDS operations complete in order) costs no
-// workgroup barrier.  0: every level uses the whole workgroup.  The results
-// are the same bits for any value (the nodes of one colour are independent);
-// the Helmholtz coarse kernel measured 22.9 / 23.5 / 24.6 / 31.3 us with 8 /
-// 0 / 16 / 32: the phases are LDS latency chains more than barrier waits.
-#ifndef WQ_COARSE_WAVE_N
-#define WQ_COARSE_WAVE_N 8
-#endif
-constexpr int kCoarseWaveN = WQ_COARSE_WAVE_N;
-
-// Level operations with the level size as a compile-time constant, run by NT
-// threads (the workgroup, or the first wavefront when NT = 64).  FAST (float
-// LDS copies, which leave room in LDS): the restriction computes each fine
-// residual once into a buffer, and the Helmholtz sweeps multiply by a stored
-// 1/D instead of dividing.
-template <typename E, bool HELM, int n, bool FAST, int NT>
-struct LdsLevel {
-    static constexpr int W = n + 1;
-    static constexpr int HALF = n / 2;                // node slots of one colour per interior row
-    static constexpr int ITEMS = (n - 1) * HALF;
-    static constexpr int NTH = NT;
-    static constexpr int PER = (ITEMS + NTH - 1) / NTH;
-
-    static __device__ __forceinline__ void sync() {
-        if constexpr (NT == 64) wave_sync();
-        else __syncthreads();
+// The same neighbours' residual f - A u; in, in0: the lane's nodes (its first
+// entry) are interior ones, 0 elsewhere.
+template <typename C, int NP>
+__device__ __forceinline__ void coarse_resid(C (&r)[NP], const C (&u)[NP], const C (&f)[NP],
+                                             const C (&D)[NP], const C (&o)[NP], C e, bool q, C ih2,
+                                             bool in, bool in0) {
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+        const C hi = m + 1 < NP ? o[m + 1 < NP ? m + 1 : m] : e, lo = m > 0 ? o[m > 0 ? m - 1 : 0] : e;
+        const C nb = lane_shift<kFromLeft>(o[m]) + lane_shift<kFromRight>(o[m]) + o[m] + (q ? hi : lo);
+        const C v = fmad(-fmad(-D[m], u[m], nb), ih2, f[m]);
+        r[m] = (m > 0 ? in : in0) ? v : C(0);
     }
+}
 
-    // nu over-relaxed red-black sweeps (sor_update); iD (FAST and HELM) =
-    // 1 / (4 + h2 k2); iDf (HELM, not FAST) = the same in float, refined by one
-    // Newton step to the precision of E instead of dividing
-    static __device__ void smooth(E* u, const E* f, const E* k2, const E* iD, const float* iDf, E h2,
-                                  E om, int nu) {
-        // slot i: row b, first node a0 = 1 + 2 (i mod HALF); colour c updates a0 + ((1 + b + c) % 2)
-        int lb[PER], pb[PER];
-        bool ok[PER], last[PER];
+// Full weighting of the residual: fine row 2J = row 2m of the lane's pair, at
+// the even columns.  An odd lane hands its three rows' weighted sum to its even
+// neighbours; e: the row 2m - 1 of the lane's first pair.  Entry m, to be used
+// on the even lanes.
+template <typename C, int NP>
+__device__ __forceinline__ void coarse_restrict(C (&v)[NP], const C (&rR)[NP], const C (&rB)[NP], C e,
+                                                bool p) {
 #pragma unroll
-        for (int m = 0; m < PER; ++m) {
-            const int i = threadIdx.x + m * NTH;
-            const int b = 1 + i / HALF;
-            const int a0 = 1 + 2 * (i - (b - 1) * HALF);
-            ok[m] = i < ITEMS;
-            last[m] = a0 == n - 1;  // a0 + 1 lies on the boundary
-            lb[m] = b * W + a0;
-            pb[m] = (1 + b) & 1;
+    for (int m = 0; m < NP; ++m) {
+        const C below = m > 0 ? (p ? rR[m > 0 ? m - 1 : 0] : rB[m > 0 ? m - 1 : 0]) : e;
+        const C s = C(2) * rB[m] + rR[m] + below;
+        v[m] = (C(4) * rR[m] + C(2) * (rB[m] + below) + lane_shift<kFromLeft>(s) +
+                lane_shift<kFromRight>(s)) * C(1.0 / 16.0);
+    }
+}
+
+// u += bilinear interpolation of the coarse correction E ((nc + 1)^2, zero
+// boundary): column I = x / 2 (the mean with I + 1 at odd x), coarse rows J0 ..
+// J0 + NP.
+template <typename C, int NP>
+__device__ __forceinline__ void coarse_prolong(C (&uR)[NP], C (&uB)[NP], const C* E, int lde, int x,
+                                               int J0, bool p) {
+    C c[NP + 1];
+    const C* q = E + J0 * lde + (x >> 1);
+#pragma unroll
+    for (int m = 0; m <= NP; ++m) c[m] = C(0.5) * (q[m * lde] + q[m * lde + (p ? 1 : 0)]);
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+        const C odd = C(0.5) * (c[m] + c[m + 1]);
+        uR[m] += p ? odd : c[m];
+        uB[m] += p ? c[m] : odd;
+    }
+}
+
+// A level of n <= 32 cells in the calling wavefront.
+template <typename C, int n>
+struct CoarseWave {
+    using L = CoarseLevel<n>;
+    static constexpr int NP = L::NP, G = L::G;
+    CoarseLds<C>& lds;
+    int lane, x, g;
+    bool p;
+    C h2, om;
+    double h;
+    __device__ __forceinline__ CoarseWave(CoarseLds<C>& l, double h_, double omega, double h2max)
+        : lds(l), lane(threadIdx.x & 63), x(lane & (n - 1)), g(lane / n), p(lane & 1), h(h_) {
+        h2 = (C)(h * h);
+        om = (C)(h * h > h2max ? 1.0 : omega);
+    }
+    __device__ __forceinline__ int row(int m, int colour) const {
+        return g * L::ROWS + 2 * m + ((p ? 1 : 0) ^ colour);
+    }
+    // entry from the neighbouring row group (0 past the last one)
+    __device__ __forceinline__ C edge(const C (&o)[NP], bool q) const {
+        const C t = q ? o[0] : o[NP - 1];
+        const C r = __shfl(t, (q ? lane + n : lane - n) & 63, 64);
+        return q && g == G - 1 ? C(0) : r;
+    }
+    __device__ __forceinline__ void table(const C* T, int colour, C (&v)[NP]) const {
+#pragma unroll
+        for (int m = 0; m < NP; ++m) v[m] = T[coarse_off_T(n) + (2 * m + colour) * 64 + lane];
+    }
+    __device__ __forceinline__ void smooth(C (&uR)[NP], C (&uB)[NP], const C (&fR)[NP], const C (&fB)[NP],
+                                           int nu) const {
+        C iR[NP], iB[NP];
+        table(lds.id, 0, iR);
+        table(lds.id, 1, iB);
+        for (int s = 0; s < nu; ++s) {
+            coarse_half<C, NP>(uR, fR, iR, uB, edge(uB, p), p, h2, om);
+            coarse_half<C, NP>(uB, fB, iB, uR, edge(uR, !p), !p, h2, om);
         }
-        for (int s = 0; s < nu; ++s)
-            for (int color = 0; color < 2; ++color) {
+    }
+    __device__ __forceinline__ void load_f(C (&fR)[NP], C (&fB)[NP]) const {
 #pragma unroll
-                for (int m = 0; m < PER; ++m) {
-                    const int d = (pb[m] + color) & 1;
-                    if (!ok[m] || (d && last[m])) continue;
-                    const int l = lb[m] + d;
-                    const E nb = u[l - 1] + u[l + 1] + u[l - W] + u[l + W];
-                    if (HELM && !FAST) {
-                        const E D = fmad(h2, k2[l], E(4));
-                        E q = (E)iDf[l];
-                        q = q * fmad(-D, q, E(2));
-                        const E g = fmad(-h2, f[l], nb) * q;
-                        u[l] = fmad(om, g - u[l], u[l]);
-                    } else {
-                        u[l] = sor_update(u[l], nb, f[l], HELM ? iD[l] : E(0.25), h2, om);
-                    }
+        for (int m = 0; m < NP; ++m) {
+            fR[m] = g < G ? lds.F[coarse_off_F(n) + min(row(m, 0), n - 1) * n + x] : C(0);
+            fB[m] = g < G ? lds.F[coarse_off_F(n) + min(row(m, 1), n - 1) * n + x] : C(0);
+        }
+    }
+    // the correction into E for the next finer level
+    __device__ __forceinline__ void store_E(const C (&uR)[NP], const C (&uB)[NP]) const {
+        if (g < G)
+#pragma unroll
+            for (int m = 0; m < NP; ++m) {
+                lds.E[coarse_off_E(n) + row(m, 0) * (n + 1) + x] = uR[m];
+                lds.E[coarse_off_E(n) + row(m, 1) * (n + 1) + x] = uB[m];
+            }
+    }
+    // V-cycle of this level and those below on u
+    __device__ __forceinline__ void cycle(C (&uR)[NP], C (&uB)[NP], const C (&fR)[NP], const C (&fB)[NP],
+                                          int nu1, int nu2, double omega, double h2max, double k2_two) const {
+        constexpr int nc = n / 2;
+        smooth(uR, uB, fR, fB, nu1);
+        C rR[NP], rB[NP];
+        {
+            C dR[NP], dB[NP];
+            table(lds.D, 0, dR);
+            table(lds.D, 1, dB);
+            const C ih2 = (C)(1.0 / (h * h));
+            const bool in = x > 0 && g < G;
+            coarse_resid<C, NP>(rR, uR, fR, dR, uB, edge(uB, p), p, ih2, in, in && (g > 0 || p));
+            coarse_resid<C, NP>(rB, uB, fB, dB, uR, edge(uR, !p), !p, ih2, in, in && (g > 0 || !p));
+        }
+        C t[NP], v[NP];
+#pragma unroll
+        for (int m = 0; m < NP; ++m) t[m] = p ? rR[m] : rB[m];
+        const C below = __shfl(t[NP - 1], (lane - n) & 63, 64);  // (row -1: only of coarse row 0)
+        coarse_restrict<C, NP>(v, rR, rB, below, p);
+        if constexpr (n == 4) {
+            // 2 x 2 cells: one unknown, four zero neighbours, solved in double
+            const double f2 = (double)__shfl(v[0], 4 + 2, 64), H = 2.0 * h;
+            if (lane == 0) lds.E[coarse_off_E(2) + 4] = (C)(-f2 / (4.0 / (H * H) + k2_two));
+            wave_sync();
+        } else {
+            if (!p && g < G)
+#pragma unroll
+                for (int m = 0; m < NP; ++m) {
+                    const int J = g * (L::ROWS / 2) + m;
+                    lds.F[coarse_off_F(nc) + J * nc + x / 2] = x > 0 && J > 0 ? v[m] : C(0);
                 }
-                sync();
-            }
-    }
-
-    static __device__ E resid(const E* u, const E* f, const E* k2, E ih2, int l) {
-        E au = (u[l - 1] + u[l + 1] + u[l - W] + u[l + W] - E(4) * u[l]) * ih2;
-        if (HELM) au -= k2[l] * u[l];
-        return f[l] - au;
-    }
-
-    // f_c = full weighting of the residual; u_c = 0.  sr (FAST): residual
-    // buffer of the level's size.
-    static __device__ void restrict_to(const E* u, const E* f, const E* k2, E ih2, E* uc, E* fc,
-                                       E* sr) {
-        constexpr int nc = n / 2, Wc = nc + 1;
-        if (FAST) {
-            for (int i = threadIdx.x; i < (n - 1) * (n - 1); i += NTH) {
-                const int y = 1 + i / (n - 1), x = 1 + i - (y - 1) * (n - 1);
-                sr[y * W + x] = resid(u, f, k2, ih2, y * W + x);
-            }
-            sync();
+            wave_sync();
+            const CoarseWave<C, nc> lc(lds, 2.0 * h, omega, h2max);
+            constexpr int NC = CoarseLevel<nc>::NP;
+            C cR[NC], cB[NC], gR[NC], gB[NC];
+#pragma unroll
+            for (int m = 0; m < NC; ++m) cR[m] = cB[m] = C(0);
+            lc.load_f(gR, gB);
+            lc.cycle(cR, cB, gR, gB, nu1, nu2, omega, h2max, k2_two);
+            lc.store_E(cR, cB);
+            wave_sync();
         }
-        for (int i = threadIdx.x; i < Wc * Wc; i += NTH) {
-            const int J = i / Wc, I = i - J * Wc;
-            E v = E(0);
-            if (I >= 1 && J >= 1 && I <= nc - 1 && J <= nc - 1) {
-                const int c = (2 * J) * W + 2 * I;
-                if (FAST)
-                    v = (E(4) * sr[c] + E(2) * (sr[c - 1] + sr[c + 1] + sr[c - W] + sr[c + W]) +
-                         (sr[c - W - 1] + sr[c - W + 1] + sr[c + W - 1] + sr[c + W + 1])) *
-                        E(1.0 / 16.0);
-                else
-                    v = (E(4) * resid(u, f, k2, ih2, c) +
-                         E(2) * (resid(u, f, k2, ih2, c - 1) + resid(u, f, k2, ih2, c + 1) +
-                                 resid(u, f, k2, ih2, c - W) + resid(u, f, k2, ih2, c + W)) +
-                         (resid(u, f, k2, ih2, c - W - 1) + resid(u, f, k2, ih2, c - W + 1) +
-                          resid(u, f, k2, ih2, c + W - 1) + resid(u, f, k2, ih2, c + W + 1))) *
-                        E(1.0 / 16.0);
-            }
-            fc[i] = v;
-            uc[i] = E(0);
-        }
-        sync();
-    }
-
-    // u += bilinear interpolation of the coarse correction uc, one coarse cell
-    // (its four fine nodes 2I..2I+1 x 2J..2J+1, interior ones only) per item
-    static __device__ void prolong_add(E* u, const E* uc) {
-        constexpr int nc = n / 2, Wc = nc + 1;
-        for (int i = threadIdx.x; i < nc * nc; i += NTH) {
-            const int J = i / nc, I = i - J * nc;
-            const int c = J * Wc + I, l = (2 * J) * W + 2 * I;
-            const E e00 = uc[c], e10 = uc[c + 1], e01 = uc[c + Wc], e11 = uc[c + Wc + 1];
-            if (I >= 1 && J >= 1) u[l] += e00;
-            if (J >= 1) u[l + 1] += E(0.5) * (e00 + e10);
-            if (I >= 1) u[l + W] += E(0.5) * (e00 + e01);
-            u[l + W + 1] += E(0.25) * (e00 + e10 + e01 + e11);
-        }
-        sync();
+        coarse_prolong<C, NP>(uR, uB, lds.E + coarse_off_E(nc), nc + 1, x, min(g, G - 1) * (L::ROWS / 2), p);
+        if (g >= G)
+#pragma unroll
+            for (int m = 0; m < NP; ++m) uR[m] = uB[m] = C(0);
+        smooth(uR, uB, fR, fB, nu2);
     }
 };
 
-// Level dispatch: runtime level size -> compile-time specialisation (for the
-// first wavefront alone only the sizes it runs).
-template <typename E, bool HELM, bool FAST, int NT, typename Fn>
-__device__ __forceinline__ void with_level(int n, Fn&& fn) {
-    constexpr int NMAX = NT == 64 ? kCoarseWaveN : 64;
-    switch (n) {
-        case 64:
-            if constexpr (NMAX >= 64) fn(LdsLevel<E, HELM, 64, FAST, NT>{});
-            break;
-        case 32:
-            if constexpr (NMAX >= 32) fn(LdsLevel<E, HELM, 32, FAST, NT>{});
-            break;
-        case 16:
-            if constexpr (NMAX >= 16) fn(LdsLevel<E, HELM, 16, FAST, NT>{});
-            break;
-        case 8:
-            if constexpr (NMAX >= 8) fn(LdsLevel<E, HELM, 8, FAST, NT>{});
-            break;
-        default:
-            if constexpr (NMAX >= 4) fn(LdsLevel<E, HELM, 4, FAST, NT>{});
-            break;
-    }
-}
-
-// All levels N <= 64 in one workgroup per right-hand side; the 2x2-cell grid
-// is solved exactly in double.  E is the type of the arrays in memory, C the
-// type of the LDS copy and of the sweep arithmetic: below a finer level the
-// result is only a coarse-grid correction, whose rounding never reaches the
-// fixed point (the finer levels' FP64 residual and smoothing set it), so it
-// runs in float there; when the coarse kernel is the whole solve, C = E.
-template <typename E, typename C, bool HELM>
-__global__ __launch_bounds__(kCoarseThreads) void k_mg_coarse(CoarseArgs<E> a) {
-    constexpr int TOT = coarse_nodes();
-    constexpr bool FAST = sizeof(C) == 4;
-    // (slot TOT of each array takes the stores of the threads past the end,
-    // so that no branch guards a store of loaded data)
-    __shared__ C su[TOT + 1];
-    __shared__ C sf[TOT + 1];
-    __shared__ C sk[HELM ? TOT + 1 : 1];
-    __shared__ C siD[(HELM && FAST) ? TOT + 1 : 1];
-    __shared__ float siDf[(HELM && !FAST) ? TOT + 1 : 1];  // float 1/D for the double sweeps
-    __shared__ C sr[FAST ? (kCoarseMax + 1) * (kCoarseMax + 1) : 1];
-    const int r = blockIdx.x;
-    const int tid = threadIdx.x;
-
-    int Ns[8], off[8], nl = 0, tot = 0;
-    for (int n = a.N; n >= 2; n /= 2) {
-        Ns[nl] = n;
-        off[nl] = tot;
-        tot += (n + 1) * (n + 1);
-        ++nl;
-    }
-    const int N = a.N;
-    // loads in batches of kB per thread so that their latencies overlap; every
-    // load and every LDS store of its value is unconditional (an index clamped
-    // into its array, the value selected after it, the store of a thread past
-    // the end going to slot TOT): a load that the compiler can move behind a
-    // lane-dependent branch is waited for before the branch ends, which would
-    // serialize the batch
-    constexpr int kB = 8;
-    const int nt = (N + 1) * (N + 1);
+// n0: cells a side of the top level.  E is the type of the arrays in memory, C
+// that of the sweeps: float where the result only corrects a finer FP64 level
+// (whose residual and smoothing set the fixed point), double elsewhere.
+template <typename E, typename C, bool HELM, int n0>
+__global__ __launch_bounds__(coarse_threads<n0>()) void k_mg_coarse(CoarseArgs<E> a) {
+    constexpr int ROWS = coarse_rows<n0>(), NP = ROWS / 2, NT = coarse_threads<n0>();
+    __shared__ CoarseLds<C> lds;
+    const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int x = n0 == 64 ? lane : lane & (n0 - 1), g = n0 == 64 ? w : lane / n0;
+    const bool p = lane & 1, live = n0 >= 16 || g < CoarseLevel<n0 == 64 ? 32 : n0>::G;
+    const C h2 = (C)(a.h * a.h), ih2 = (C)(1.0 / (a.h * a.h));
+    const C om = (C)(a.h * a.h > a.h2max ? 1.0 : a.omega);
+    // the top level's nodes (row y of entry m): every load unconditional, from
+    // clamped indices, and masked after
+    C uR[NP], uB[NP], fR[NP], fB[NP], iR[NP], iB[NP], dR[NP], dB[NP];
     const bool has_u = a.u_init[r] != nullptr;
     const E* ui = has_u ? a.u_init[r] : a.f[r];
-    const E* fi = a.f[r];
-    // (the values are masked by a product with 0 or 1, not a select: the
-    // compiler turns a select between a loaded value and a constant into a
-    // branch around the load; every value loaded here is finite)
-    const auto load_uf = [&](int i, E& uo, E& fo) {
-        const int ic = min(i, nt - 1);
-        const int y = ic / (N + 1), x = ic - y * (N + 1);
-        const size_t g = (size_t)y * a.pitch + x;
-        const E ut = ui[g], ft = fi[g];
-        const bool ok = i < nt && x != 0 && y != 0 && x != N && y != N;
-        uo = ut * E(ok && has_u ? 1 : 0);
-        fo = ft * E(ok ? 1 : 0);
+    const C* top_D = coarse_tab<C>(a.tab.D, a.tab.Df);
+    const C* top_id = coarse_tab<C>(a.tab.id, a.tab.idf);
+    const auto load = [&](int m, int colour, C& u, C& f, C& id, C& D) {
+        const int y = min(g * ROWS + 2 * m + ((p ? 1 : 0) ^ colour), n0 - 1);
+        const size_t i = (size_t)y * a.pitch + x;
+        const bool in = live && x > 0 && y > 0;
+        u = (C)ui[i] * C(in && has_u ? 1 : 0);
+        f = (C)a.f[r][i] * C(in ? 1 : 0);
+        if (HELM) {
+            const int k = y * (n0 + 1) + x;
+            id = top_id[k] * C(in ? 1 : 0);
+            D = top_D[k];
+        } else {
+            id = in ? C(0.25) : C(0);
+            D = C(4);
+        }
     };
-    if (HELM && tot <= kB * kCoarseThreads) {
-        // one batch: u, f, k2 and 1/D all issued before the first LDS store
-        // (k2 in the type of the sweeps; 1/D always from the float table)
-        E uv[kB], fv[kB];
-        C kv[kB];
-        float dv[kB];
 #pragma unroll
-        for (int b = 0; b < kB; ++b) {
-            const int i = b * kCoarseThreads + tid, ic = min(i, tot - 1);
-            load_uf(i, uv[b], fv[b]);
-            kv[b] = FAST ? (C)a.k2levf[ic] : (C)a.k2lev[ic];
-            dv[b] = a.idlevf[ic];
-        }
-#pragma unroll
-        for (int b = 0; b < kB; ++b) {
-            const int i = b * kCoarseThreads + tid;
-            const int iu = i < nt ? i : TOT, ik = i < tot ? i : TOT;
-            su[iu] = (C)uv[b];
-            sf[iu] = (C)fv[b];
-            sk[ik] = kv[b];
-            if (FAST) siD[ik] = (C)dv[b];
-            else siDf[ik] = dv[b];
-        }
-    } else {
-        for (int base = 0; base < nt; base += kB * kCoarseThreads) {
-            E uv[kB], fv[kB];
-#pragma unroll
-            for (int b = 0; b < kB; ++b) load_uf(base + b * kCoarseThreads + tid, uv[b], fv[b]);
-#pragma unroll
-            for (int b = 0; b < kB; ++b) {
-                const int i = base + b * kCoarseThreads + tid, iu = i < nt ? i : TOT;
-                su[iu] = (C)uv[b];
-                sf[iu] = (C)fv[b];
-            }
-        }
-        if (HELM)  // k2 and 1/D of every level, made once per solve by k_coarse_k2
-            for (int base = 0; base < tot; base += kB * kCoarseThreads) {
-                C kv[kB];
-                float dv[kB];
-#pragma unroll
-                for (int b = 0; b < kB; ++b) {
-                    const int i = base + b * kCoarseThreads + tid, ic = min(i, tot - 1);
-                    kv[b] = FAST ? (C)a.k2levf[ic] : (C)a.k2lev[ic];
-                    dv[b] = a.idlevf[ic];
-                }
-#pragma unroll
-                for (int b = 0; b < kB; ++b) {
-                    const int i = base + b * kCoarseThreads + tid, ik = i < tot ? i : TOT;
-                    sk[ik] = kv[b];
-                    if (FAST) siD[ik] = (C)dv[b];
-                    else siDf[ik] = dv[b];
-                }
-            }
+    for (int m = 0; m < NP; ++m) {
+        load(m, 0, uR[m], fR[m], iR[m], dR[m]);
+        load(m, 1, uB[m], fB[m], iB[m], dB[m]);
     }
-    __syncthreads();
+    // 1/D and D of the levels in one wavefront, in their lane layout
+    {
+        constexpr int T0 = n0 == 64 ? 0 : coarse_off_T(n0), IT = (kCoarseT - T0) / NT;
+        static_assert((kCoarseT - T0) % NT == 0, "whole trips");
+        const C* tid_ = coarse_tab<C>(a.tab.Tid, a.tab.Tidf) + T0;
+        const C* tD = coarse_tab<C>(a.tab.TD, a.tab.TDf) + T0;
+        C vi[IT], vD[IT];
+#pragma unroll
+        for (int q = 0; q < IT; ++q) {
+            const int i = tid + q * NT;
+            if (HELM) {
+                vi[q] = tid_[i];
+                vD[q] = tD[i];
+            } else {
+                vi[q] = C(coarse_slot(T0 + i).in ? 0.25 : 0.0);
+                vD[q] = C(4);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < IT; ++q) {
+            lds.id[T0 + tid + q * NT] = vi[q];
+            lds.D[T0 + tid + q * NT] = vD[q];
+        }
+    }
+    const double k2_two = HELM ? a.tab.TD[kCoarseT] : 0.0;  // node (1, 1) of the 2-cell level
+    for (int i = tid; i < coarse_off_E(1); i += NT) lds.E[i] = C(0);
+    if constexpr (n0 == 64)
+        for (int i = tid; i < 2 * 64; i += NT)  // past the first and last wavefront
+            lds.edge[i >> 6][0][i & 63] = lds.edge[i >> 6][kCoarseWaves + 1][i & 63] = C(0);
+    if constexpr (n0 == 64) __syncthreads();
+    else wave_sync();
 
-    auto down = [&](int l, auto nt) {
-        constexpr int NT = decltype(nt)::value;
-        const double hl = a.h * (double)(1 << l);
-        C* u = su + off[l];
-        C* f = sf + off[l];
-        const C* k2 = sk + (HELM ? off[l] : 0);
-        const C* iD = siD + ((HELM && FAST) ? off[l] : 0);
-        const float* iDf = siDf + ((HELM && !FAST) ? off[l] : 0);
-        with_level<C, HELM, FAST, NT>(Ns[l], [&](auto L) {
-            L.smooth(u, f, k2, iD, iDf, (C)(hl * hl), (C)(HELM && hl * hl > a.h2max ? 1.0 : a.omega), a.nu1);
-            L.restrict_to(u, f, k2, (C)(1.0 / (hl * hl)), su + off[l + 1], sf + off[l + 1], sr);
-        });
-    };
-    auto up = [&](int l, auto nt) {
-        constexpr int NT = decltype(nt)::value;
-        const double hl = a.h * (double)(1 << l);
-        C* u = su + off[l];
-        with_level<C, HELM, FAST, NT>(Ns[l], [&](auto L) {
-            L.prolong_add(u, su + off[l + 1]);
-            L.smooth(u, sf + off[l], sk + (HELM ? off[l] : 0), siD + ((HELM && FAST) ? off[l] : 0),
-                     siDf + ((HELM && !FAST) ? off[l] : 0), (C)(hl * hl),
-                     (C)(HELM && hl * hl > a.h2max ? 1.0 : a.omega), a.nu2);
-        });
-    };
-    const std::integral_constant<int, kCoarseThreads> all{};
-    const std::integral_constant<int, 64> wave{};
-    // levels lw and below (at most kCoarseWaveN cells a side) in the first
-    // wavefront; the workgroup's barriers before and after hand the LDS over
-    int lw = 0;
-    while (lw < nl - 1 && Ns[lw] > kCoarseWaveN) ++lw;
-    for (int cyc = 0; cyc < a.ncycles; ++cyc) {
-        for (int l = 0; l < lw; ++l) down(l, all);
-        if (tid < 64) {
-            for (int l = lw; l < nl - 1; ++l) down(l, wave);
-            if (tid == 0) {  // 2x2 cells: one unknown, four zero neighbours
-                const int l = nl - 1;
-                const double hl = a.h * (double)(1 << l);
-                const int c = 1 * 3 + 1;
-                const double k2c = HELM ? (double)sk[off[l] + c] : 0.0;
-                su[off[l] + c] = (C)(-(double)sf[off[l] + c] / (4.0 / (hl * hl) + k2c));
-            }
-            wave_sync();
-            for (int l = nl - 2; l >= lw; --l) up(l, wave);
+    int buf = 0;
+    // the row across the boundary to the next wavefront (64^2) or group
+    const auto edge = [&](const C (&o)[NP], bool q) -> C {
+        if constexpr (n0 == 64) {
+            lds.edge[buf][w + 1][lane] = q ? o[0] : o[NP - 1];
+            __syncthreads();
+            const C e = lds.edge[buf][q ? w + 2 : w][lane];
+            buf ^= 1;
+            return e;
+        } else {
+            const C t = q ? o[0] : o[NP - 1];
+            const C e = __shfl(t, (q ? lane + n0 : lane - n0) & 63, 64);
+            return q && g == CoarseLevel<n0>::G - 1 ? C(0) : e;
         }
-        __syncthreads();
-        for (int l = lw - 1; l >= 0; --l) up(l, all);
+    };
+    const auto residual = [&](C (&rR)[NP], C (&rB)[NP]) {
+        const bool in = x > 0 && live;
+        coarse_resid<C, NP>(rR, uR, fR, dR, uB, edge(uB, p), p, ih2, in, in && (g > 0 || p));
+        coarse_resid<C, NP>(rB, uB, fB, dB, uR, edge(uR, !p), !p, ih2, in, in && (g > 0 || !p));
+    };
+    const auto norms = [&](int slot) {
+        C rR[NP], rB[NP];
+        residual(rR, rB);
+        double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            s[0] += (double)rR[m] * rR[m] + (double)rB[m] * rB[m];
+            s[1] += (double)fR[m] * fR[m] + (double)fB[m] * fB[m];
+            s[2] += (double)uR[m] * uR[m] + (double)uB[m] * uB[m];
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], d, 64);
+        if constexpr (n0 == 64) {
+            if (lane == 0)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) lds.red[w][q] = s[q];
+            __syncthreads();
+            if (tid < 3) {
+                double t = 0.0;
+                for (int k = 0; k < kCoarseWaves; ++k) t += lds.red[k][tid];
+                a.norm_part[slot * a.norm_stride + 3 * r + tid] = t;
+            }
+        } else if (lane < 3) {
+            a.norm_part[slot * a.norm_stride + 3 * r + lane] = lane == 0 ? s[0] : lane == 1 ? s[1] : s[2];
+        }
+    };
+    const auto smooth = [&](int nu) {
+        for (int k = 0; k < nu; ++k) {
+            coarse_half<C, NP>(uR, fR, iR, uB, edge(uB, p), p, h2, om);
+            coarse_half<C, NP>(uB, fB, iB, uR, edge(uR, !p), !p, h2, om);
+        }
+    };
+    for (int cyc = 0; cyc < a.ncycles; ++cyc) {
+        if (a.norm_part) norms(cyc);
+        for (int k = 0; k < a.inner; ++k) {
+            if constexpr (n0 < 64) {
+                const CoarseWave<C, n0> top(lds, a.h, a.omega, a.h2max);
+                top.cycle(uR, uB, fR, fB, a.nu1, a.nu2, a.omega, a.h2max, k2_two);
+            } else {
+                smooth(a.nu1);
+                C rR[NP], rB[NP], t[NP], v[NP];
+                residual(rR, rB);
+#pragma unroll
+                for (int m = 0; m < NP; ++m) t[m] = p ? rR[m] : rB[m];
+                const C below = edge(t, false);  // row -1 of the first wavefront: 0
+                coarse_restrict<C, NP>(v, rR, rB, below, p);
+                if (!p)
+#pragma unroll
+                    for (int m = 0; m < NP; ++m) {
+                        const int J = w * NP + m;
+                        lds.F[J * 32 + x / 2] = x > 0 && J > 0 ? v[m] : C(0);
+                    }
+                __syncthreads();
+                if (w == 0) {
+                    const CoarseWave<C, 32> lc(lds, 2.0 * a.h, a.omega, a.h2max);
+                    constexpr int NC = CoarseLevel<32>::NP;
+                    C cR[NC], cB[NC], gR[NC], gB[NC];
+#pragma unroll
+                    for (int m = 0; m < NC; ++m) cR[m] = cB[m] = C(0);
+                    lc.load_f(gR, gB);
+                    lc.cycle(cR, cB, gR, gB, a.nu1, a.nu2, a.omega, a.h2max, k2_two);
+                    lc.store_E(cR, cB);
+                }
+                __syncthreads();
+                coarse_prolong<C, NP>(uR, uB, lds.E, 33, x, w * NP, p);
+                smooth(a.nu2);
+            }
+        }
     }
-    for (int i = tid; i < (N + 1) * (N + 1); i += kCoarseThreads) {
-        const int y = i / (N + 1), x = i - y * (N + 1);
-        a.u_out[r][(size_t)y * a.pitch + x] = (E)su[i];
-    }
+    if (a.norm_part) norms(a.ncycles);
+    if (live)
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const int y = g * ROWS + 2 * m;
+            a.u_out[r][(size_t)(y + (p ? 1 : 0)) * a.pitch + x] = (E)uR[m];
+            a.u_out[r][(size_t)(y + (p ? 0 : 1)) * a.pitch + x] = (E)uB[m];
+        }
 }
 
 // Exact solve of the Poisson problem on the 64^2 coarse level (u = 0 on the
@@ -1655,31 +1758,32 @@ __global__ void k_dst_tables(int n, double H, float* S, float* M, double* S64, d
     }
 }
 
-// k2 of the coarse-kernel levels: the top level (N <= 64, pitched) copied
-// densely, then full weighting level by level.  One block.
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse_k2(int N, int pitch, double h,
-                                                              const double* __restrict__ k2top,
-                                                              double* __restrict__ out,
-                                                              float* __restrict__ outf,
-                                                              float* __restrict__ idf) {
+// The coarse kernel's tables from k2 on its top level (N <= 64, pitched), the
+// coarser levels by full weighting: D = 4 + h^2 k2 and 1/D on the top level
+// (dense [N+1]^2) and, in their lane layout, on the levels of at most 32 cells
+// (T; entry kCoarseT of TD: k2 at the one node of the 2-cell level).  One block.
+constexpr int kK2Threads = 1024;
+__global__ __launch_bounds__(kK2Threads) void k_coarse_k2(int N, int pitch, double h,
+                                                          const double* __restrict__ k2top,
+                                                          CoarseTabs t) {
     // every level in LDS: the top level's loads in batches of kB per thread,
     // the restrictions from LDS, the three outputs written once
-    __shared__ double sk[coarse_nodes()];
+    __shared__ double sk[65 * 65 + coarse_off_E(1)];
     constexpr int kB = 8;
     const int tid = threadIdx.x;
     const int nt = (N + 1) * (N + 1);
-    for (int base = 0; base < nt; base += kB * kCoarseThreads) {
+    for (int base = 0; base < nt; base += kB * kK2Threads) {
         double v[kB];
 #pragma unroll
         for (int b = 0; b < kB; ++b) {
-            const int i = base + b * kCoarseThreads + tid;
+            const int i = base + b * kK2Threads + tid;
             const int y = i / (N + 1), x = i - y * (N + 1);
             const bool ok = i < nt && x != 0 && y != 0 && x != N && y != N;
             v[b] = ok ? k2top[(size_t)y * pitch + x] : 0.0;
         }
 #pragma unroll
         for (int b = 0; b < kB; ++b) {
-            const int i = base + b * kCoarseThreads + tid;
+            const int i = base + b * kK2Threads + tid;
             if (i < nt) sk[i] = v[b];
         }
     }
@@ -1689,7 +1793,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_k2(int N, int pitch, 
         const int nc = nf / 2, w = nf + 1;
         const double* kf = sk + off;
         double* kc = sk + off + (nf + 1) * (nf + 1);
-        for (int i = tid; i < (nc + 1) * (nc + 1); i += kCoarseThreads) {
+        for (int i = tid; i < (nc + 1) * (nc + 1); i += kK2Threads) {
             const int J = i / (nc + 1), I = i - J * (nc + 1);
             double v = 0.0;
             if (I >= 1 && J >= 1 && I <= nc - 1 && J <= nc - 1) {
@@ -1703,21 +1807,26 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_k2(int N, int pitch, 
         __syncthreads();
         off += (nf + 1) * (nf + 1);
     }
-    // double and float copies and 1 / (4 + h_l^2 k2) for the coarse kernel's
-    // FP32 sweeps
-    off = 0;
-    for (int n = N, l = 0; n >= 2; n /= 2, ++l) {
-        const double hl = h * (double)(1 << l);
-        const float h2 = (float)(hl * hl);
-        for (int i = tid; i < (n + 1) * (n + 1); i += kCoarseThreads) {
-            const double kd = sk[off + i];
-            const float kf = (float)kd;
-            out[off + i] = kd;
-            outf[off + i] = kf;
-            idf[off + i] = 1.f / (4.f + h2 * kf);
-        }
-        off += (n + 1) * (n + 1);
+    const auto put = [](double k2, double h2, double in, double& D, double& id, float& Df, float& idf) {
+        const double Dd = fmad(h2, k2, 4.0);
+        const float Ds = 4.f + (float)h2 * (float)k2;
+        D = Dd;
+        id = in / Dd;
+        Df = Ds;
+        idf = (float)in / Ds;
+    };
+    for (int i = tid; i < (N + 1) * (N + 1); i += kK2Threads)
+        put(sk[i], h * h, 1.0, t.D[i], t.id[i], t.Df[i], t.idf[i]);
+    for (int i = tid; i < kCoarseT; i += kK2Threads) {
+        const CoarseSlot c = coarse_slot(i);
+        if (c.n > N) continue;  // a level above the top one
+        int o = 0;
+        for (int n = N; n > c.n; n /= 2) o += (n + 1) * (n + 1);
+        const double hl = h * (double)(N / c.n);
+        put(sk[o + min(c.y, c.n) * (c.n + 1) + c.x], hl * hl, c.in ? 1.0 : 0.0, t.TD[i], t.Tid[i],
+            t.TDf[i], t.Tidf[i]);
     }
+    if (tid == 0) t.TD[kCoarseT] = sk[off + 4];  // off: the 2-cell level
 }
 
 // Residual norms of the current iterate, one partial sum per interior row and
@@ -1781,17 +1890,6 @@ __global__ __launch_bounds__(kThreads) void k_resnorm(int N, double ih2, int pit
         for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], d, 64);
     if (lane < 3)
         part[(size_t)(3 * r + lane) * nblk + row - 1] = lane == 0 ? s[0] : lane == 1 ? s[1] : s[2];
-}
-
-// Mixed form: u += e on the interior nodes (the FP32 correction added in FP64).
-__global__ void k_correct(int N, int pitch, int pitch32, double* __restrict__ u0,
-                          double* __restrict__ u1, const float* __restrict__ e0,
-                          const float* __restrict__ e1) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = blockIdx.y;
-    if (a < 1 || a > N - 1 || b < 1 || b > N - 1) return;
-    u0[(size_t)b * pitch + a] += (double)e0[(size_t)b * pitch32 + a];
-    if (u1) u1[(size_t)b * pitch + a] += (double)e1[(size_t)b * pitch32 + a];
 }
 
 // The norms of a batch of V-cycles to the host: one workgroup per slot and
@@ -1887,8 +1985,6 @@ void up(int R, bool helm, const UpArgs<E>& a, int nu, dim3 g, hipStream_t s, con
     if (R == 1) helm ? launch_up<E, 1, true>(a, nu, g, s, ps, T) : launch_up<E, 1, false>(a, nu, g, s, ps, T);
     else helm ? launch_up<E, 2, true>(a, nu, g, s, ps, T) : launch_up<E, 2, false>(a, nu, g, s, ps, T);
 }
-
-dim3 tiles(int N, int T = kTile) { return dim3((N + T - 1) / T, (N + T - 1) / T); }
 
 // Tiles of a level's down or up pass: register tiles on the levels
 // N >= c->reg_tile_min, LDS tiles of edge tile_for(N) below.  TX x TY owned
@@ -2039,7 +2135,55 @@ template <> float* lev_f<float>(wq::Level& L, int r) { return L.f32[r]; }
 
 int nu_pre_at(const wandqs_ctx* c, int l) { return l >= kFullPreLevels ? 1 : c->cfg.nu_pre; }
 
-// One V-cycle on levels 0..L.  zero_guess: the level-0 iterate starts from 0.
+// The arguments of k_mg_coarse that do not depend on the launch (top level: lev[lc]).
+template <typename E>
+void coarse_args(wandqs_ctx* c, CoarseArgs<E>& a, bool helm) {
+    const wq::Level& L = c->lev[c->lc];
+    a.h = L.h;
+    a.pitch = L.pitch;
+    a.tab = c->ctab;
+    a.omega = helm ? c->cfg.mg_omega_helm : c->cfg.mg_omega;
+    a.h2max = helm ? kOmegaH2N0 / c->cfg.n0 : std::numeric_limits<double>::infinity();
+    a.nu2 = c->cfg.nu_post;
+}
+
+// ncycles (times inner) V-cycles of a whole solve on a grid of at most 64^2 in
+// one launch; slot >= 0: the norms before each of them and after the last go to
+// the slots from it on, one partial each.
+void whole_cycles(wandqs_ctx* c, int R, bool helm, const Hier<double>& hz, int ncycles, int inner,
+                  int slot) {
+    CoarseArgs<double> a{};
+    coarse_args(c, a, helm);
+    for (int r = 0; r < R; ++r) {
+        a.f[r] = hz.f0[r];
+        a.u_init[r] = hz.u0[r];
+        a.u_out[r] = hz.u0[r];
+    }
+    a.ncycles = ncycles;
+    a.inner = inner;
+    a.nu1 = nu_pre_at(c, 0);
+    a.norm_stride = (size_t)kNormVec * c->max_tiles;
+    a.norm_part = slot >= 0 ? c->norm_part + slot * a.norm_stride : nullptr;
+    const double nodes = (double)(c->N + 1) * (c->N + 1);
+    char nm[64];
+    prof_name(c, nm, sizeof nm, "k_mg_coarse<double, double, %s, %d>", helm ? "true" : "false", c->N);
+    ProfScope ps(c, nm, nodes * (24.0 * R + (helm ? 16.0 : 0.0)));
+#define WQ_WHOLE(n)                                                                                  \
+    do {                                                                                             \
+        const dim3 b(coarse_threads<n>());                                              \
+        if (helm) WQ_KLAUNCH(ps, (k_mg_coarse<double, double, true, n>), dim3(R), b, 0, c->stream, a); \
+        else WQ_KLAUNCH(ps, (k_mg_coarse<double, double, false, n>), dim3(R), b, 0, c->stream, a);   \
+    } while (0)
+    switch (c->N) {
+        case 8: WQ_WHOLE(8); break;
+        case 16: WQ_WHOLE(16); break;
+        case 32: WQ_WHOLE(32); break;
+        default: WQ_WHOLE(64); break;
+    }
+#undef WQ_WHOLE
+}
+
+// One V-cycle on levels 0..L (grids above 64^2).  zero_guess: the level-0 iterate starts from 0.
 // norm_slot >= 0 (double only) records the residual of the incoming iterate.
 template <typename E>
 void vcycle(wandqs_ctx* c, int R, bool helm, const Hier<E>& hz, bool zero_guess, int norm_slot,
@@ -2106,27 +2250,10 @@ void vcycle(wandqs_ctx* c, int R, bool helm, const Hier<E>& hz, bool zero_guess,
         E* uo[2] = {U(1, 0), R > 1 ? U(1, 1) : nullptr};
         fst_solve<E>(c, R, fo, uo);
     } else {
-        wq::Level& L = c->lev[lc];
-        CoarseArgs<E> a{};
-        a.omega = om;
-        a.h2max = h2max;
-        a.N = L.N;
-        a.h = L.h;
-        a.pitch = L.pitch;
-        for (int r = 0; r < R; ++r) {
-            a.f[r] = F(lc, r);
-            a.u_init[r] = (lc == 0 && !zero_guess) ? hz.u0[r] : nullptr;
-            a.u_out[r] = U(lc, r);
-        }
-        a.k2lev = helm ? c->k2lev : nullptr;
-        a.k2levf = helm ? c->k2levf : nullptr;
-        a.idlevf = helm ? c->idlevf : nullptr;
-        a.ncycles = WQ_COARSE_CYCLES;
-        a.nu1 = nu_pre_at(c, lc);
-        a.nu2 = c->cfg.nu_post;
+        wq::Level& L = c->lev[lc];  // 64^2
         const double nodes = (double)(L.N + 1) * (L.N + 1);
         char nm[64];
-        if (!helm && lc > 0 && L.N == kDstN && coarse64) {  // exact Poisson coarse solve, FP64
+        if (!helm && coarse64) {  // exact Poisson coarse solve, FP64
             DstArgs64<E> d{};
             d.pitch = L.pitch;
             for (int r = 0; r < R; ++r) {
@@ -2137,7 +2264,7 @@ void vcycle(wandqs_ctx* c, int R, bool helm, const Hier<E>& hz, bool zero_guess,
             d.M = c->dst_M64;
             ProfScope ps(c, "k_coarse_dst64<float>", nodes * 2.0 * eb * R + 2.0 * 8.0 * kDstN * kDstN);
             WQ_KLAUNCH(ps, k_coarse_dst64<E>, dim3(R), dim3(1024), 0, s, d);
-        } else if (!helm && lc > 0 && L.N == kDstN) {  // exact Poisson coarse solve
+        } else if (!helm) {  // exact Poisson coarse solve
             DstArgs<E> d{};
             d.pitch = L.pitch;
             for (int r = 0; r < R; ++r) {
@@ -2150,22 +2277,20 @@ void vcycle(wandqs_ctx* c, int R, bool helm, const Hier<E>& hz, bool zero_guess,
             ProfScope ps(c, nm, nodes * 2.0 * eb * R + 2.0 * 4.0 * kDstN * kDstN);
             WQ_KLAUNCH(ps, k_coarse_dst<E>, dim3(R), dim3(1024), 0, s, d);
         } else {
-            // float sweeps when the coarse levels only correct a finer FP64
-            // level; the mixed form's inner cycles run them in double
-            const bool f32 = WQ_COARSE_F32 && lc > 0 && !coarse64;
-            prof_name(c, nm, sizeof nm, "k_mg_coarse<%s, %s, %s>", type_name(E()),
-                          f32 ? "float" : (coarse64 ? "double" : type_name(E())), helm ? "true" : "false");
-            ProfScope ps(c, nm, nodes * (eb * R + (a.u_init[0] ? eb * R : 0.0) + (helm ? 8.0 : 0.0) + eb * R));
-            if (coarse64) {
-                if (helm) WQ_KLAUNCH(ps, (k_mg_coarse<E, double, true>), dim3(R), dim3(kCoarseThreads), 0, s, a);
-                else WQ_KLAUNCH(ps, (k_mg_coarse<E, double, false>), dim3(R), dim3(kCoarseThreads), 0, s, a);
-            } else if (f32) {
-                if (helm) WQ_KLAUNCH(ps, (k_mg_coarse<E, float, true>), dim3(R), dim3(kCoarseThreads), 0, s, a);
-                else WQ_KLAUNCH(ps, (k_mg_coarse<E, float, false>), dim3(R), dim3(kCoarseThreads), 0, s, a);
-            } else {
-                if (helm) WQ_KLAUNCH(ps, (k_mg_coarse<E, E, true>), dim3(R), dim3(kCoarseThreads), 0, s, a);
-                else WQ_KLAUNCH(ps, (k_mg_coarse<E, E, false>), dim3(R), dim3(kCoarseThreads), 0, s, a);
+            // float sweeps, as they only correct a finer FP64 level; double in
+            // the mixed form's inner cycles, whose finer levels are in float
+            using CT = typename std::conditional<coarse64, double, float>::type;
+            CoarseArgs<E> a{};
+            coarse_args(c, a, helm);
+            for (int r = 0; r < R; ++r) {
+                a.f[r] = F(lc, r);
+                a.u_out[r] = U(lc, r);
             }
+            a.ncycles = a.inner = 1;
+            a.nu1 = nu_pre_at(c, lc);
+            prof_name(c, nm, sizeof nm, "k_mg_coarse<%s, %s, true, 64>", type_name(E()), type_name(CT()));
+            ProfScope ps(c, nm, nodes * (2.0 * eb * R + 2.0 * sizeof(CT)));
+            WQ_KLAUNCH(ps, (k_mg_coarse<E, CT, true, 64>), dim3(R), dim3(coarse_threads<64>()), 0, s, a);
         }
     }
     for (int l = lb - 1; l >= 0; --l) {
@@ -2271,16 +2396,10 @@ void mixed_iteration(wandqs_ctx* c, int R, bool helm, const Hier<double>& hz, in
     resnorm(c, R, helm, hz, slot, hf.f0);
     const int inner = c->cfg.mg_inner_cycles > 0 ? c->cfg.mg_inner_cycles : 1;
     // the last inner cycle's finest up pass adds its result to the FP64
-    // iterate (u += e) itself, unless level 0 is the coarse kernel's
+    // iterate (u += e) itself
     double* const corr[2] = {hz.u0[0], R > 1 ? hz.u0[1] : nullptr};
-    const bool fused = c->lc > 0;
     for (int i = 0; i < inner; ++i)
-        vcycle<float>(c, R, helm, hf, i == 0, -1, -1, fused && i == inner - 1 ? corr : nullptr);
-    if (fused) return;
-    ProfScope ps(c, "k_correct", (double)L0.N * L0.N * 20.0 * R);
-    WQ_KLAUNCH(ps, k_correct, dim3((L0.N + 1 + 127) / 128, L0.N + 1), dim3(128), 0, c->stream,
-                       L0.N, L0.pitch, L0.pitch, hz.u0[0], R > 1 ? hz.u0[1] : nullptr, L0.u32[0],
-                       R > 1 ? L0.u32[1] : nullptr);
+        vcycle<float>(c, R, helm, hf, i == 0, -1, -1, i == inner - 1 ? corr : nullptr);
 }
 
 }  // namespace
@@ -2397,11 +2516,9 @@ wandqs_status helm_levels(wandqs_ctx* c, const double* k2) {
         // k2 of the coarse-kernel levels, once per solve
         const wq::Level& T = c->lev[c->lc];
         const double* top = c->lc == 0 ? k2 : T.k2;
-        int tot = 0;
-        for (int n = T.N; n >= 2; n /= 2) tot += (n + 1) * (n + 1);
-        ProfScope ps(c, "k_coarse_k2", 24.0 * tot);
-        WQ_KLAUNCH(ps, k_coarse_k2, dim3(1), dim3(kCoarseThreads), 0, s, T.N, T.pitch, T.h, top,
-                           c->k2lev, c->k2levf, c->idlevf);
+        ProfScope ps(c, "k_coarse_k2", 32.0 * (T.N + 1) * (T.N + 1) + 24.0 * kCoarseT);
+        WQ_KLAUNCH(ps, k_coarse_k2, dim3(1), dim3(kK2Threads), 0, s, T.N, T.pitch, T.h, top,
+                           c->ctab);
     }
     WQ_LAUNCH_CHECK();
     return WANDQS_OK;
@@ -2412,7 +2529,11 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
                        const std::function<wandqs_status()>& ahead, bool k2_levels_ready) {
     hipStream_t s = c->stream;
     Hier<double> hz{{u[0], R > 1 ? u[1] : nullptr}, {f[0], R > 1 ? f[1] : nullptr}, k2};
-    const bool mixed = c->cfg.precision == WANDQS_MIXED;
+    // grids of at most 64^2 run whole in the coarse kernel, in double in both
+    // forms (a mixed iteration is then its inner cycles)
+    const bool whole = c->lc == 0;
+    const bool mixed = c->cfg.precision == WANDQS_MIXED && !whole;
+    const int inner = c->cfg.precision == WANDQS_MIXED ? std::max(1, c->cfg.mg_inner_cycles) : 1;
     const bool direct = direct_poisson(c, helm);
     if (helm && !k2_levels_ready) {
         const wandqs_status st = helm_levels(c, k2);
@@ -2441,12 +2562,10 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
         c->err = std::string("hipGraphLaunch: ") + hipGetErrorString(gerr);
         return WANDQS_E_HIP;
     };
-    // the down pass records the incoming residual itself unless the top level is
-    // the coarse kernel (FP64) ; the mixed defect kernel always records it
-    const bool separate_norm = !mixed && c->lc == 0;
     const int maxc = c->cfg.mg_max_cycles;
     if (!(c->cfg.mg_rtol > 0.0)) {
-        for (int k = 0; k < maxc; ++k) cycle(mixed ? 0 : -1, -1, FuseCtl{});
+        if (whole) whole_cycles(c, R, helm, hz, maxc, inner, -1);
+        else for (int k = 0; k < maxc; ++k) cycle(mixed ? 0 : -1, -1, FuseCtl{});
         if (graph_check() != WANDQS_OK) return WANDQS_E_HIP;
         WQ_LAUNCH_CHECK();
         if (res) *res = SolveResult{maxc, {-1.0, -1.0}};
@@ -2456,14 +2575,14 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     const double atol = c->cfg.mg_atol * std::sqrt((double)(N - 1) * (N - 1));
     // partial sums of the norms per slot
     // (the V-cycles' down passes: one per level-0 tile; resnorm and the sine
-    // transform solve: one per interior row)
+    // transform solve: one per interior row; whole solves in one workgroup: one)
     const dim3 g = pass_geom(c, N, nu_pre_at(c, 0), true).grid;
-    const int nblk = mixed || direct || separate_norm ? N - 1 : g.x * g.y;
+    const int nblk = whole ? 1 : mixed || direct ? N - 1 : g.x * g.y;
     // the batch's last cycle records the final norms in its finest up pass
     // (register tiles, FP64) instead of a separate residual pass
     const PassGeom gu = pass_geom(c, N, c->cfg.nu_post, false, true);
-    const bool up_norms = !mixed && !direct && !separate_norm && gu.reg;
-    const int nblk_up = up_norms ? (int)(gu.grid.x * gu.grid.y) : N - 1;
+    const bool up_norms = !mixed && !direct && !whole && gu.reg;
+    const int nblk_up = up_norms ? (int)(gu.grid.x * gu.grid.y) : whole ? 1 : N - 1;
     // inside a batch, each cycle's level-0 up pass but the last fuses with the
     // next cycle's down pass; their norm slots have the fused launch's tiles
     const bool fuse = !mixed && up_norms && fuse_possible(c);
@@ -2476,22 +2595,21 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     constexpr int V = kNormVec;
     const double a_norm = 8.0 / (c->lev[0].h * c->lev[0].h);  // ||L_h||_2 bound
     const double eps = std::numeric_limits<double>::epsilon();
-    if (separate_norm) resnorm(c, R, helm, hz, 0, nullptr);
     while (true) {
         int b = done == 0 ? pred : 1;
         if (done + b > maxc) b = maxc - done;
-        for (int k = 0; k < b; ++k) {
+        if (whole) whole_cycles(c, R, helm, hz, b, inner, done);
+        for (int k = 0; k < b && !whole; ++k) {
             const int cyc = done + k;
             FuseCtl fz;
             fz.skip_down0 = fuse && k > 0;
             fz.fuse_up0 = fuse && k < b - 1;
             fz.next_slot = cyc + 1;
             fz.cur = cur;
-            cycle(mixed || c->lc > 0 ? cyc : -1, up_norms && k == b - 1 ? cyc + 1 : -1, fz);
+            cycle(cyc, up_norms && k == b - 1 ? cyc + 1 : -1, fz);
             if (fz.fuse_up0) cur ^= 1;
-            if (separate_norm) resnorm(c, R, helm, hz, cyc + 1, nullptr);
         }
-        if (!separate_norm && !up_norms) resnorm(c, R, helm, hz, done + b, nullptr);
+        if (!whole && !up_norms) resnorm(c, R, helm, hz, done + b, nullptr);
         const int s0 = done == 0 ? 0 : done + 1;
         const int ns = done + b + 1 - s0;
         if (graph_check() != WANDQS_OK) return WANDQS_E_HIP;

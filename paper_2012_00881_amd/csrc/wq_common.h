@@ -17,10 +17,7 @@ namespace wq {
 constexpr int kMaxBeams = 8;
 constexpr int kMaxProbes = 16;
 constexpr int kMaxLevels = 13;
-#ifndef WQ_COARSE_MAX
-#define WQ_COARSE_MAX 64
-#endif
-constexpr int kCoarseMax = WQ_COARSE_MAX;  // levels with N <= kCoarseMax are solved inside one workgroup
+constexpr int kCoarseMax = 64;  // levels with N <= kCoarseMax are solved inside one workgroup
 constexpr int kMaxSlots = 208;  // residual-norm records per solve (mg_max_cycles + batches)
 constexpr int kNormVec = 6;     // per record and right-hand side r: sums of r^2, f^2, u^2 at 3r .. 3r+2
 // Rounding-floor test of the stop rule: ||r|| <= kFloorBE eps (||L_h|| ||u|| + ||f||).
@@ -100,6 +97,15 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// Tables of the coarse Helmholtz levels (<= 64^2), in double and in float:
+// D = 4 + h^2 k2 and 1/D on the top one (dense [65][65] at most) and, for the
+// levels of at most 32 cells, in the lane layout of the coarse kernel (T).
+constexpr int kCoarseTop = 65 * 65, kCoarseTab = 1536 + 8;
+struct CoarseTabs {
+    double *D, *id, *TD, *Tid;
+    float *Df, *idf, *TDf, *Tidf;
+};
 
 enum SolveKind {
     kSolvePsi = 0,
@@ -286,9 +292,7 @@ struct wandqs_ctx {
     double* nu_tab = nullptr;
     double* nu_part = nullptr;
     double* nu_red = nullptr;
-    double* k2lev = nullptr;  // k2 of the coarse-kernel levels (dense, concatenated)
-    float* k2levf = nullptr;  // the same in float, and 1 / (4 + h_l^2 k2) in float
-    float* idlevf = nullptr;
+    wq::CoarseTabs ctab{};  // the coarse kernel's tables of the Helmholtz operator
     // exact Poisson solve on the 64^2 coarse level: sine-transform matrix S and
     // the scaled inverse eigenvalues M, [64][64] float each (zero row/column 63)
     float* dst_S = nullptr;
