@@ -481,7 +481,7 @@ size_t wq::carve(wandqs_ctx* c, char* base) {
     }
     c->nu_tab = (double*)take(sizeof(double) * nu_table_doubles(c->N));
     c->nu_part = (double*)take(sizeof(double) * 3 * (size_t)(c->N + 1));
-    c->nu_red = (double*)take(sizeof(double) * 4);
+    c->nu_coarse_m = (double*)take(sizeof(double) * 1600);
     c->cell_count = (int32_t*)take(sizeof(int32_t) * ncell);
     c->cell_start = (int32_t*)take(sizeof(int32_t) * (ncell + 1));
     c->big_cells = (int32_t*)take(sizeof(int32_t) * ncell);

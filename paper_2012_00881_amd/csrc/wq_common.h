@@ -288,10 +288,10 @@ struct wandqs_ctx {
     double* las_part = nullptr;
     double* las_red = nullptr;
     // non-uniform grid solver (wandqs_nu_mg_solve): the per-level 1-D tables,
-    // the norm partials [3][N-1] and their sums [3]
+    // the norm partials [N-1][3]
     double* nu_tab = nullptr;
     double* nu_part = nullptr;
-    double* nu_red = nullptr;
+    double* nu_coarse_m = nullptr;  // M restricted to the levels of at most 32 cells
     wq::CoarseTabs ctab{};  // the coarse kernel's tables of the Helmholtz operator
     // exact Poisson solve on the 64^2 coarse level: sine-transform matrix S and
     // the scaled inverse eigenvalues M, [64][64] float each (zero row/column 63)
@@ -405,6 +405,9 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
                        double* const f[2], const double* k2, SolveResult* res,
                        const std::function<wandqs_status()>& ahead = {},
                        bool k2_levels_ready = false);
+// Waits until the device has published sequence number seq at h_seq (pinned,
+// coherent).
+wandqs_status wait_published(wandqs_ctx* c, const uint32_t* h_seq, uint32_t seq);
 // The Helmholtz operator's k2 on the coarser levels (full weighting level by
 // level, then the coarse kernel's dense levels), from the finest level's k2.
 wandqs_status helm_levels(wandqs_ctx* c, const double* k2);
