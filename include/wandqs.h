@@ -176,8 +176,9 @@ typedef struct {
                              or iterations of the exact sine-transform solve (see wandqs_mg_solve) */
     double rel_resid[5];  /* final ||r||/||f|| per field; -1 if not tracked */
     int32_t flags;        /* bit 0: 1+psi <= 0 met */
-    int32_t laser_vcycles; /* multigrid cycles of the envelope plane this slice advanced
-                              (time loop with a laser), else 0 */
+    int32_t laser_vcycles; /* multigrid cycles (or sine-transform iterations, see
+                              wandqs_laser_set) of the envelope plane this slice
+                              advanced (time loop with a laser), else 0 */
 } wandqs_slice_info;
 
 /* Bytes of device workspace needed for cfg and runs of up to n_slices slices
@@ -281,7 +282,12 @@ wandqs_status wandqs_driver_set(wandqs_ctx* ctx, int64_t n, const double* d_stat
  *   L_h a1 - (chi + beta - i gam) a1 = (chi - beta + i gam) a0 - L_h a0 - beta (p1 - p0),
  * beta = 4/(dt dxi0), gam = 4 k0/dt, a1 = 0 on the boundary, by multigrid
  * with the context's mg_* stop rule, from the guess a0; chi = n* / (1 + psi)
- * is the plasma's susceptibility.
+ * is the plasma's susceptibility.  On grids of 128^2 .. 2048^2 a plane whose
+ * chi varies over its nodes by no more than 0.4 |kbar| on either side of the
+ * middle of its range, kbar = that middle + beta - i gam, is solved by
+ * iterations with an exact FP64 sine-transform solve of L_h - kbar instead of
+ * V-cycles (where mg_max_cycles leaves room for them), to the same stop rule; an
+ * iteration then counts as a cycle.
  *
  * wandqs_laser_advance(dt, d_chi, h_cycles) advances every plane by dt > 0
  * with chi given on the device as [laser_nz][N+1][N+1] doubles (NULL:

@@ -373,11 +373,11 @@ void carve_dst(wandqs_ctx* c, Take&& take, bool top) {
     c->dst_M64 = mixed ? (double*)take(sizeof(double) * 64 * 64) : nullptr;
     top = top && wq::fst_top_used(c);
     if (top || wq::fst_used(c)) {
-        const size_t n = c->lev[top ? 0 : 1].N;
-        for (int r = 0; r < 2; ++r) {
-            c->fst_t1[r] = (double*)take(sizeof(double) * (n - 1) * (n + 8));
-            c->fst_t2[r] = (double*)take(sizeof(double) * (n - 1) * (n + 8));
-        }
+        const size_t n = c->lev[top ? 0 : 1].N, one = (n - 1) * (n + 8);
+        c->fst_t1[0] = (double*)take(sizeof(double) * 2 * one);
+        c->fst_t2[0] = (double*)take(sizeof(double) * 2 * one);
+        c->fst_t1[1] = c->fst_t1[0] + one;
+        c->fst_t2[1] = c->fst_t2[0] + one;
     }
     if (top) {
         c->fst_top_tw = (double2*)take(sizeof(double2) * 2 * (size_t)c->N);
@@ -476,8 +476,7 @@ size_t wq::carve(wandqs_ctx* c, char* base) {
             c->las_f[l] = carr(l);
             c->las_k[l] = carr(l);
         }
-        c->las_part = (double*)take(sizeof(double) * 4 * (size_t)(c->N + 1));
-        c->las_red = (double*)take(sizeof(double) * 4);
+        c->las_part = (double*)take(sizeof(double) * 8 * (size_t)(c->N + 1));
     }
     c->nu_tab = (double*)take(sizeof(double) * nu_table_doubles(c->N));
     c->nu_part = (double*)take(sizeof(double) * 3 * (size_t)(c->N + 1));

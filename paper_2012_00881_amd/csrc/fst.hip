@@ -467,6 +467,181 @@ void launch_fst(wandqs_ctx* c, const FstArgs<E>& a, int R, const char* tname) {
     }
 }
 
+// ------------------------------------------------- laser envelope planes --
+
+// One iteration u += (L_h - kbar)^-1 (f - (L_h - k) u) of a laser envelope plane
+// (complex, (re, im) pairs): L_h - kbar with a constant kbar = kr - i gam is
+// diagonal under the sine transform, eigenvalue lambda_kl - kr + i gam.  The
+// passes are those of k_fst on the real and the imaginary part of a row, one
+// wavefront each: T1 and T2 hold (re, im) pairs, so that the transposed writes
+// of the x and y passes go out in 32-byte pieces (two rows per workgroup), and
+// the y pass exchanges the parts' coefficients through LDS for the complex
+// division.  At 512^2 x 9.1, y 11.1, x inverse 6.9 us (1.8, 0.75 and 1.8 TB/s of
+// its bytes; the two transforms of the y pass and its scattered writes bound
+// that one).  A plane of a pulse with the plasma behind its front (512^2) takes
+// 6 of these instead of 9.4 V-cycles of 95 us: its time step of 20 planes 31.2
+// -> 15.5 ms.
+struct LasFstArgs {
+    int pitch, ld;
+    const double2* f;
+    const double2* k;
+    double2* u;
+    double* t1;
+    double* t2;
+    const double2* tw;
+    const double* s2;
+    double lam, scale, ih2;
+    double kr, gam;
+};
+
+template <int LOGN, int MODE>
+constexpr int las_rows() { return MODE < 2 && LOGN <= 10 ? 2 : 1; }
+
+template <int LOGN, int MODE>
+__global__ __launch_bounds__((128 * las_rows<LOGN, MODE>())) void k_las_fst(LasFstArgs a) {
+    using F = FstSize<LOGN>;
+    constexpr int n = F::n, H = F::H, NB = F::NB, PER = F::PER, LP = F::LP;
+    constexpr int RW = las_rows<LOGN, MODE>();
+    __shared__ double bufs[2 * RW][4 * LP];
+    __shared__ double2 T[H];
+    int pb, r0;
+    tile_of_block(pb, r0);
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, part = w & 1, t = threadIdx.x & 127;
+    const bool live = pb * RW + (w >> 1) < n - 1;
+    const int p = live ? pb * RW + (w >> 1) : n - 2;
+    double* buf = bufs[w];
+    double *V0 = bufs[w & ~1], *V1 = bufs[w | 1];  // the row's real and imaginary part
+    double2 tv[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) tv[q] = a.tw[2 * (lane + 64 * q)];
+    double sn[NB][4][2];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int m = min(lane + 64 * b, H / 4 - 1) + s * (H / 4);
+                sn[b][s][e] = -a.tw[2 * m + e].y;
+            }
+    const size_t ld = a.ld;
+    double xe[PER], xo[PER];
+    if constexpr (MODE == 0) {
+        // the row's residual, node j = t + 128 q (node 0 is a boundary node)
+        const size_t g0 = (size_t)(p + 1) * a.pitch;
+        const double2 *u = a.u + g0, *f = a.f + g0, *k = a.k + g0;
+        constexpr int Q = n / 128, CH = Q < 2 ? Q : 2;
+#pragma unroll
+        for (int q0 = 0; q0 < Q; q0 += CH) {
+            double2 c[CH], l[CH], r[CH], up[CH], dn[CH], fv[CH], kv[CH];
+#pragma unroll
+            for (int q = 0; q < CH; ++q) {
+                const int j = t + 128 * (q0 + q);
+                c[q] = u[j];
+                l[q] = u[max(j - 1, 0)];
+                r[q] = u[j + 1];
+                up[q] = u[j - a.pitch];
+                dn[q] = u[j + a.pitch];
+                fv[q] = f[j];
+                kv[q] = k[j];
+            }
+#pragma unroll
+            for (int q = 0; q < CH; ++q) {
+                const int j = t + 128 * (q0 + q);
+                const double in = j > 0 ? 1.0 : 0.0;
+                const double lx = a.ih2 * (l[q].x + r[q].x + up[q].x + dn[q].x - 4.0 * c[q].x);
+                const double ly = a.ih2 * (l[q].y + r[q].y + up[q].y + dn[q].y - 4.0 * c[q].y);
+                V0[pidx(j)] = in * (fv[q].x - (lx - (kv[q].x * c[q].x - kv[q].y * c[q].y)));
+                V1[pidx(j)] = in * (fv[q].y - (ly - (kv[q].x * c[q].y + kv[q].y * c[q].x)));
+            }
+        }
+        __syncthreads();
+        const auto get = [=](int j) { return buf[pidx(j)]; };
+        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+    } else {
+        const double* row = (MODE == 1 ? a.t1 : a.t2) + 2 * ((size_t)p * ld - 1) + part;
+        const auto get = [=](int j) { return row[2 * j]; };
+        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+    }
+    if constexpr (MODE == 1) {
+        // coefficient (k, l) over its eigenvalue er + i gam, then back along y
+        const double lk = a.lam * a.s2[p + 1] - a.kr;
+        const double sg = part ? -a.gam : a.gam;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int k = lane * PER + q;
+            buf[pidx(2 * k)] = xe[q];
+            buf[pidx(2 * k + 1)] = xo[q];
+        }
+        __syncthreads();
+        const double* o = bufs[w ^ 1];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int k = lane * PER + q;
+            const double e0 = lk + a.lam * a.s2[2 * k], e1 = lk + a.lam * a.s2[2 * k + 1];
+            xe[q] = k == 0 ? 0.0 : (xe[q] * e0 + sg * o[pidx(2 * k)]) / (e0 * e0 + sg * sg);
+            xo[q] = (xo[q] * e1 + sg * o[pidx(2 * k + 1)]) / (e1 * e1 + sg * sg);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int k = lane * PER + q;
+            buf[pidx(2 * k)] = xe[q];
+            buf[pidx(2 * k + 1)] = xo[q];
+        }
+        wave_sync();
+        const auto get = [=](int j) { return buf[pidx(j)]; };
+        wdst<LOGN, false>(get, sn, buf, T, tv, xe, xo);
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int k = lane * PER + q;
+        buf[pidx(2 * k)] = k == 0 ? 0.0 : xe[q];
+        buf[pidx(2 * k + 1)] = xo[q];
+    }
+    __syncthreads();
+    if constexpr (MODE < 2) {
+        // coefficient c (1 .. n-1) of the workgroup's rows: T[c - 1][row] = (re, im)
+        double* Tt = (MODE == 0 ? a.t1 : a.t2) + 2 * (size_t)(pb * RW);
+        for (int i = threadIdx.x; i < (n - 1) * 2 * RW; i += 128 * RW) {
+            const int c = 1 + i / (2 * RW), ww = i % (2 * RW);
+            if (pb * RW + (ww >> 1) < n - 1) Tt[2 * (size_t)(c - 1) * ld + ww] = bufs[ww][pidx(c)];
+        }
+    } else {
+        double2* row = a.u + (size_t)(p + 1) * a.pitch;
+        constexpr int Q = n / 128;
+        double2 uv[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) uv[q] = row[t + 128 * q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int j = t + 128 * q;
+            uv[q].x += a.scale * V0[pidx(j)];
+            uv[q].y += a.scale * V1[pidx(j)];
+            row[j] = uv[q];
+        }
+    }
+}
+
+template <int LOGN>
+void launch_las_fst(wandqs_ctx* c, const LasFstArgs& a) {
+    constexpr int n = 1 << LOGN, RW = las_rows<LOGN, 0>();
+    const double nodes = (double)(n - 1) * (n - 1);
+    const dim3 gw((n - 1 + RW - 1) / RW);
+    {
+        ProfScope ps(c, "k_las_fst<x>", nodes * 64.0);
+        WQ_KLAUNCH(ps, (k_las_fst<LOGN, 0>), gw, dim3(128 * RW), 0, c->stream, a);
+    }
+    {
+        ProfScope ps(c, "k_las_fst<y>", nodes * 32.0);
+        WQ_KLAUNCH(ps, (k_las_fst<LOGN, 1>), gw, dim3(128 * RW), 0, c->stream, a);
+    }
+    {
+        ProfScope ps(c, "k_las_fst<xinv>", nodes * 48.0);
+        WQ_KLAUNCH(ps, (k_las_fst<LOGN, 2>), dim3(n - 1), dim3(128), 0, c->stream, a);
+    }
+}
+
 __global__ void k_fst_tables(int L, double2* tw, double* s2) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < L) {
@@ -526,6 +701,32 @@ void fst_top_iteration(wandqs_ctx* c, int R, const double* const* f, double* con
         case 512: launch_fst<double, 9, true>(c, a, R, "top"); break;
         case 1024: launch_fst<double, 10, true>(c, a, R, "top"); break;
         default: launch_fst<double, 11, true>(c, a, R, "top"); break;
+    }
+}
+
+void las_fst_iteration(wandqs_ctx* c, const double2* f, const double2* k, double2* u, double kr, double gam) {
+    const Level& L0 = c->lev[0];
+    LasFstArgs a{};
+    a.pitch = L0.pitch;
+    a.ld = L0.N + 8;
+    a.f = f;
+    a.k = k;
+    a.u = u;
+    a.t1 = c->fst_t1[0];  // the two right-hand sides' arrays, contiguous
+    a.t2 = c->fst_t2[0];
+    a.tw = c->fst_top_tw;
+    a.s2 = c->fst_top_s2;
+    a.lam = -4.0 / (L0.h * L0.h);
+    a.scale = (2.0 / L0.N) * (2.0 / L0.N);
+    a.ih2 = 1.0 / (L0.h * L0.h);
+    a.kr = kr;
+    a.gam = gam;
+    switch (L0.N) {
+        case 128: launch_las_fst<7>(c, a); break;
+        case 256: launch_las_fst<8>(c, a); break;
+        case 512: launch_las_fst<9>(c, a); break;
+        case 1024: launch_las_fst<10>(c, a); break;
+        default: launch_las_fst<11>(c, a); break;
     }
 }
 

@@ -14,7 +14,9 @@
 // already at t + dt when the sweep reaches plane j):
 //   L_h a1 - (chi + beta - i gam) a1 = (chi - beta + i gam) a0 - L_h a0 - beta (p1 - p0),
 //   beta = 4/(dt dxi0), gam = 4 k0/dt,  a1 = 0 on the boundary,
-// chi = n* / (1 + psi) at the nodes.  It is solved by a complex multigrid:
+// chi = n* / (1 + psi) at the nodes.  Where chi varies little against beta - i gam
+// (las_shift) it is solved by sine-transform iterations (fst.hip), else by a
+// complex multigrid:
 // V(nu_pre, nu_post) cycles of red-black Gauss-Seidel on the levels above
 // kLasCoarse (per level one fused down pass -- the pre-sweeps, the residual
 // and its full weighting, on LDS tiles with halos -- and one fused up pass --
@@ -428,62 +430,71 @@ __global__ __launch_bounds__(kLasThreads) void k_las_coarse(int n0, double h0, i
     }
 }
 
-// Per node row b: sums over the interior nodes of (f_re^2, f_im^2) (mode 0) or
-// of (r_re^2, r_im^2, u_re^2, u_im^2), r = f - (L_h u - k u) (mode 1).
-__global__ __launch_bounds__(kNormThreads) void k_las_norm(int n, int pitch, double ih2, int mode,
+// Norms of the level-0 problem: [f_re^2, f_im^2, r_re^2, r_im^2, u_re^2, u_im^2,
+// min Re k, max Re k] over the interior nodes, r = f - (L_h u - k u).  One
+// workgroup per node row, then k_las_norm_fin over the rows.
+constexpr int kNormVals = 8;
+__device__ __forceinline__ double norm_join(int q, double a, double b) {
+    return q == 6 ? fmin(a, b) : q == 7 ? fmax(a, b) : a + b;
+}
+// Joins the threads' values in a fixed order; thread 0 holds the result.
+__device__ __forceinline__ void norm_block(double (&s)[kNormVals], double* red) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+        for (int q = 0; q < kNormVals; ++q) s[q] = norm_join(q, s[q], __shfl_xor(s[q], d, 64));
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int q = 0; q < kNormVals; ++q) red[kNormVals * (threadIdx.x >> 6) + q] = s[q];
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kNormThreads / 64; ++w)
+#pragma unroll
+            for (int q = 0; q < kNormVals; ++q) s[q] = norm_join(q, s[q], red[kNormVals * w + q]);
+}
+__global__ __launch_bounds__(kNormThreads) void k_las_norm(int n, int pitch, double ih2,
                                                            const double2* __restrict__ u,
                                                            const double2* __restrict__ f,
                                                            const double2* __restrict__ k,
                                                            double* __restrict__ part) {
-    __shared__ double red[4][kNormThreads];
+    __shared__ double red[kNormVals * kNormThreads / 64];
     const int b = blockIdx.x + 1;  // rows 1 .. n-1
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    double s[kNormVals] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, INFINITY, -INFINITY};
     for (int a = 1 + threadIdx.x; a <= n - 1; a += kNormThreads) {
         const size_t i = (size_t)b * pitch + a;
-        if (mode == 0) {
-            const double2 v = f[i];
-            s[0] += v.x * v.x;
-            s[1] += v.y * v.y;
-        } else {
-            const double2 r = resid_at(u, f, k, i, pitch, ih2);
-            const double2 w = u[i];
-            s[0] += r.x * r.x;
-            s[1] += r.y * r.y;
-            s[2] += w.x * w.x;
-            s[3] += w.y * w.y;
-        }
+        const double2 r = resid_at(u, f, k, i, pitch, ih2), v = f[i], w = u[i];
+        const double x = k[i].x;
+        s[0] += v.x * v.x;
+        s[1] += v.y * v.y;
+        s[2] += r.x * r.x;
+        s[3] += r.y * r.y;
+        s[4] += w.x * w.x;
+        s[5] += w.y * w.y;
+        s[6] = fmin(s[6], x);
+        s[7] = fmax(s[7], x);
     }
+    norm_block(s, red);
+    if (threadIdx.x == 0)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) red[q][threadIdx.x] = s[q];
-    __syncthreads();
-    for (int w = kNormThreads / 2; w >= 1; w >>= 1) {
-        if (threadIdx.x < w)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) part[(size_t)4 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
+        for (int q = 0; q < kNormVals; ++q) part[(size_t)kNormVals * blockIdx.x + q] = s[q];
 }
 
-// Sum of the row partials (rows in order within each thread, then a fixed
-// tree): out[q] for q = 0..3.
+// The rows' values into the host's coherent pinned array, then the sequence
+// number that tells the host so.
 __global__ __launch_bounds__(kNormThreads) void k_las_norm_fin(int rows, const double* __restrict__ part,
-                                                               double* __restrict__ out) {
-    __shared__ double red[4][kNormThreads];
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
+                                                               double* out, uint32_t* dst_seq, uint32_t seq) {
+    __shared__ double red[kNormVals * kNormThreads / 64];
+    double s[kNormVals] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, INFINITY, -INFINITY};
     for (int r = threadIdx.x; r < rows; r += kNormThreads)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) s[q] += part[(size_t)4 * r + q];
+        for (int q = 0; q < kNormVals; ++q) s[q] = norm_join(q, s[q], part[(size_t)kNormVals * r + q]);
+    norm_block(s, red);
+    if (threadIdx.x == 0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) red[q][threadIdx.x] = s[q];
-    __syncthreads();
-    for (int w = kNormThreads / 2; w >= 1; w >>= 1) {
-        if (threadIdx.x < w)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
-        __syncthreads();
+        for (int q = 0; q < kNormVals; ++q) out[q] = s[q];
+        __threadfence_system();
+        __hip_atomic_store(dst_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    if (threadIdx.x < 4) out[threadIdx.x] = red[threadIdx.x][0];
 }
 
 // Dense [N+1][N+1] complex <-> padded plane.
@@ -500,24 +511,24 @@ __global__ void k_las_pack(int N, int pitch, const double2* __restrict__ src, do
 
 dim3 rows_grid(int n, int t) { return dim3((n + 1 + t - 1) / t, n + 1); }
 
-// Residual norms of the level-0 problem: out = {||.||^2 ...} as k_las_norm.
-wandqs_status las_norms(wandqs_ctx* c, int mode, const double2* u, const double2* f,
-                        const double2* k, double* out4) {
+// Norms of the level-0 problem (as k_las_norm) into out[kNormVals]; waits for them.
+wandqs_status las_norms(wandqs_ctx* c, const double2* u, const double2* f, const double2* k, double* out) {
     const Level& L0 = c->lev[0];
     const int rows = L0.N - 1;
+    uint32_t* h_seq = reinterpret_cast<uint32_t*>(c->h_pin + kMaxSlots * kNormVec + 1);
+    const uint32_t seq = ++c->pub_seq;
     {
-        ProfScope ps(c, "k_las_norm", (double)(L0.N + 1) * (L0.N + 1) * (mode ? 48.0 : 16.0));
+        ProfScope ps(c, "k_las_norm", (double)(L0.N + 1) * (L0.N + 1) * 48.0);
         WQ_KLAUNCH(ps, k_las_norm, dim3(rows), dim3(kNormThreads), 0, c->stream, L0.N, L0.pitch,
-                   1.0 / (L0.h * L0.h), mode, u, f, k, c->las_part);
+                   1.0 / (L0.h * L0.h), u, f, k, c->las_part);
     }
     {
-        ProfScope ps(c, "k_las_norm_fin", 32.0 * rows);
+        ProfScope ps(c, "k_las_norm_fin", 8.0 * kNormVals * rows);
         WQ_KLAUNCH(ps, k_las_norm_fin, dim3(1), dim3(kNormThreads), 0, c->stream, rows, c->las_part,
-                   c->las_red);
+                   out, h_seq, seq);
     }
     WQ_LAUNCH_CHECK();
-    WQ_HIP(hipMemcpyAsync(out4, c->las_red, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    return WANDQS_OK;
+    return wait_published(c, h_seq, seq);
 }
 
 wandqs_status las_vcycle(wandqs_ctx* c, double2* u0) {
@@ -563,6 +574,28 @@ wandqs_status laser_nodes(wandqs_ctx* c) {
     return node_gradient(c, c->las_a2, c->las_g[0], c->las_g[1]);
 }
 
+namespace {
+// How a plane is solved.  The operator L_h - k differs from L_h - kbar, which a
+// sine-transform iteration inverts exactly (las_fst_iteration), only by k - kbar:
+// with kbar = kr - i gam, kr the middle of Re k's range on the interior nodes, an
+// iteration multiplies the residual's 2-norm by rho = (half the range) /
+// |kr - i gam| at most, as -L_h > 0.  A V-cycle gains a factor 20 to 25 and takes
+// 95 us at 512^2, an iteration 27 us, so the iterations are taken up to rho = 0.4, where they gain
+// as much per time, if mg_max_cycles leaves room for the count that rho ensures
+// (to 1e-16).  An unbounded or undefined k goes to the V-cycles.
+constexpr double kLasDirectRho = 0.4;
+struct LasShift {
+    bool direct;
+    double kr;
+};
+LasShift las_shift(const wandqs_ctx* c, double kmin, double kmax, double gam) {
+    const double kr = 0.5 * (kmin + kmax), rho = 0.5 * (kmax - kmin) / std::hypot(kr, gam);
+    if (!c->fst_top_tw || !(kr >= 0.0) || !(rho <= kLasDirectRho)) return {false, 0.0};
+    const double need = rho > 1e-16 ? std::ceil(std::log(1e-16) / std::log(rho)) : 1.0;
+    return {need + 2.0 <= c->cfg.mg_max_cycles, kr};
+}
+}  // namespace
+
 wandqs_status laser_plane_advance(wandqs_ctx* c, double dt, const double* chi, int j, int* cycles) {
     const Level& L0 = c->lev[0];
     const size_t plane = (size_t)(L0.N + 1) * L0.pitch;
@@ -578,55 +611,65 @@ wandqs_status laser_plane_advance(wandqs_ctx* c, double dt, const double* chi, i
         WQ_KLAUNCH(ps, k_las_rhs, rows_grid(L0.N, 128), dim3(128), 0, c->stream, L0.N, L0.h, L0.pitch,
                    beta, gam, chi, a0, p0, p1, c->las_f[0], c->las_k[0], u);
     }
-    for (int l = 1; l <= c->las_ll; ++l) {
-        const Level& F = c->lev[l - 1];
-        const Level& C = c->lev[l];
-        ProfScope ps(c, "k_las_krestrict", (double)(F.N + 1) * (F.N + 1) * 16.0 + (double)(C.N + 1) * (C.N + 1) * 16.0);
-        WQ_KLAUNCH(ps, k_las_krestrict, rows_grid(C.N, 128), dim3(128), 0, c->stream, C.N, F.pitch,
-                   c->las_k[l - 1], C.pitch, c->las_k[l]);
-    }
     WQ_LAUNCH_CHECK();
     // the stop rule of the multigrid solves, on the real and imaginary parts
-    double* hn = c->h_pin + kMaxSlots * kNormVec + 8;  // [fn re, fn im, -, -, r re, r im, u re, u im]
+    double* hn = c->h_pin + kMaxSlots * kNormVec + 8;  // as k_las_norm
     wandqs_status s;
-    if ((s = las_norms(c, 0, u, c->las_f[0], c->las_k[0], hn)) != WANDQS_OK) return s;
-    if ((s = las_norms(c, 1, u, c->las_f[0], c->las_k[0], hn + 4)) != WANDQS_OK) return s;
-    WQ_HIP(hipStreamSynchronize(c->stream));
+    if ((s = las_norms(c, u, c->las_f[0], c->las_k[0], hn)) != WANDQS_OK) return s;
+    const LasShift sh = las_shift(c, hn[6], hn[7], gam);
+    if (!sh.direct)
+        for (int l = 1; l <= c->las_ll; ++l) {
+            const Level& F = c->lev[l - 1];
+            const Level& C = c->lev[l];
+            ProfScope ps(c, "k_las_krestrict", (double)(F.N + 1) * (F.N + 1) * 16.0 + (double)(C.N + 1) * (C.N + 1) * 16.0);
+            WQ_KLAUNCH(ps, k_las_krestrict, rows_grid(C.N, 128), dim3(128), 0, c->stream, C.N, F.pitch,
+                       c->las_k[l - 1], C.pitch, c->las_k[l]);
+        }
     const double eps = std::numeric_limits<double>::epsilon();
     const double a_norm = 8.0 / (L0.h * L0.h);
     const double nint = (double)(L0.N - 1) * (L0.N - 1);
-    double fn[2], rn[2], rprev[2], tol[2], scale[2];
+    double fn[2], rn[2], tol[2], goal[2], scale[2];
     bool done[2];
     for (int q = 0; q < 2; ++q) {
         fn[q] = std::sqrt(hn[q]);
-        rn[q] = rprev[q] = std::sqrt(hn[4 + q]);
+        rn[q] = std::sqrt(hn[2 + q]);
         tol[q] = c->cfg.mg_rtol * (fn[q] > 0 ? fn[q] : rn[q]) + c->cfg.mg_atol * std::sqrt(nint);
         scale[q] = std::max(fn[q], rn[q]);
         done[q] = rn[q] <= tol[q];
     }
     int cyc = 0;
     // the first batch runs one cycle fewer than the last plane needed (planes
-    // next to each other converge alike), then one cycle per norm check
-    int batch = std::max(1, c->las_pred - 1);
+    // next to each other converge alike); after a norm check the next batch is
+    // what the rate of the last one leaves to do, rounded down
+    int batch = std::max(1, c->las_pred[sh.direct] - 1);
     while (!(done[0] && done[1]) && cyc < c->cfg.mg_max_cycles) {
         const int b = std::min(batch, c->cfg.mg_max_cycles - cyc);
-        for (int q = 0; q < b; ++q)
-            if ((s = las_vcycle(c, u)) != WANDQS_OK) return s;
+        for (int q = 0; q < b; ++q) {
+            if (sh.direct) las_fst_iteration(c, c->las_f[0], c->las_k[0], u, sh.kr, gam);
+            else if ((s = las_vcycle(c, u)) != WANDQS_OK) return s;
+        }
+        WQ_LAUNCH_CHECK();
         cyc += b;
-        batch = 1;
-        if ((s = las_norms(c, 1, u, c->las_f[0], c->las_k[0], hn + 4)) != WANDQS_OK) return s;
-        WQ_HIP(hipStreamSynchronize(c->stream));
+        const double rp[2] = {rn[0], rn[1]};
+        if ((s = las_norms(c, u, c->las_f[0], c->las_k[0], hn)) != WANDQS_OK) return s;
         for (int q = 0; q < 2; ++q) {
-            rprev[q] = rn[q];
-            rn[q] = std::sqrt(hn[4 + q]);
-            const double un = std::sqrt(hn[6 + q]);
-            if (rn[q] <= tol[q] || rn[q] <= kFloorBE * eps * (a_norm * un + fn[q])) done[q] = true;
-            else if (cyc >= 2 && rn[q] > 0.5 * rprev[q] && rn[q] <= 1e-9 * scale[q]) done[q] = true;
-            else done[q] = false;
+            rn[q] = std::sqrt(hn[2 + q]);
+            goal[q] = std::max(tol[q], kFloorBE * eps * (a_norm * std::sqrt(hn[4 + q]) + fn[q]));
+        }
+        // the iterations' contraction is that of both parts together, so that
+        // one part alone may stand still for an iteration without stagnating
+        const bool still = std::hypot(rn[0], rn[1]) > 0.5 * std::hypot(rp[0], rp[1]);
+        batch = c->cfg.mg_max_cycles;
+        for (int q = 0; q < 2; ++q) {
+            done[q] = rn[q] <= goal[q] || (cyc >= 2 && rn[q] <= 1e-9 * scale[q] &&
+                                           (sh.direct ? still : rn[q] > 0.5 * rp[q]));
+            if (done[q]) continue;
+            const double left = b * std::log(goal[q] / rn[q]) / std::log(rn[q] / rp[q]);
+            batch = std::min(batch, left >= 2.0 && left < batch ? (int)left : 1);
         }
     }
     if (cycles) *cycles = cyc;
-    c->las_pred = cyc;
+    c->las_pred[sh.direct] = cyc;
     if (!(std::isfinite(rn[0]) && std::isfinite(rn[1]) && done[0] && done[1])) {
         c->err = "laser envelope: multigrid did not converge";
         return WANDQS_E_NOCONV;

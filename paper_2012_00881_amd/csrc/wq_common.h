@@ -277,7 +277,8 @@ struct wandqs_ctx {
     double las_dt = 0.0;
     int las_j = 0;            // plane of the next slice in the time step's sweep
     int las_cycles = 0;       // multigrid cycles of the last plane advanced
-    int las_pred = 1;         // cycles the last solved plane needed (first batch size)
+    // cycles the last solved plane needed (first batch size): V-cycles, sine-transform iterations
+    int las_pred[2] = {1, 1};
     double* las_a2 = nullptr;
     double* las_g[2] = {};
     double2* las_u[wq::kMaxLevels] = {};
@@ -286,7 +287,6 @@ struct wandqs_ctx {
     double2* las_k[wq::kMaxLevels] = {};
     int las_ll = 0;           // level solved (with those below) by one workgroup
     double* las_part = nullptr;
-    double* las_red = nullptr;
     // non-uniform grid solver (wandqs_nu_mg_solve): the per-level 1-D tables,
     // the norm partials [N-1][3]
     double* nu_tab = nullptr;
@@ -394,6 +394,9 @@ void fst_solve(wandqs_ctx* c, int R, const E* const* f, E* const* u);
 bool fst_top_used(const wandqs_ctx* c);
 void fst_top_iteration(wandqs_ctx* c, int R, const double* const* f, double* const* u,
                        double* norm_part);
+// One iteration u += (L_h - kr + i gam)^-1 (f - (L_h - k) u) of a laser envelope
+// plane by sine transforms (grids with fst_top_tw).
+void las_fst_iteration(wandqs_ctx* c, const double2* f, const double2* k, double2* u, double kr, double gam);
 
 // multigrid (mg.hip)
 // ahead (optional): work that reads the solution but does not change what the

@@ -417,7 +417,7 @@ class Simulation:
 
     def laser_advance(self, dt: float, chi=None):
         """Advance the envelope by dt with the susceptibility chi
-        [laser_nz][N+1][N+1] (None: vacuum); returns the V-cycles per plane."""
+        [laser_nz][N+1][N+1] (None: vacuum); returns the V-cycles (or iterations) per plane."""
         t = self.torch
         nz = int(self.cfg["laser_nz"])
         ch = None
