@@ -134,6 +134,7 @@ void set_sizes(wandqs_ctx* c, const wandqs_config* cfg, int32_t n_slices) {
         const char* e = std::getenv("WANDQS_MG_TILES");
         c->reg_tile_min = (e && std::strcmp(e, "lds") == 0) ? INT_MAX : wq::reg_tile_min_default();
         if (e && std::atoi(e) >= 8) c->reg_tile_min = std::atoi(e);  // smallest register-tile level
+        c->top_tile_min = e ? c->reg_tile_min : wq::top_tile_min_default();
         const char* st = std::getenv("WANDQS_MG_SMALL");
         c->small_tile_max = st && std::atoi(st) >= 8 ? std::atoi(st) : wq::small_tile_max_default();
         const char* sp = std::getenv("WANDQS_MG_SPLIT");
@@ -411,7 +412,7 @@ size_t wq::carve(wandqs_ctx* c, char* base) {
         for (int k = 0; k < 5; ++k) c->fields_prev3[k] = arr(0);
     for (int r = 0; r < 2; ++r) {
         L0.um[r] = arr(0);
-        L0.um2[r] = c->N >= c->reg_tile_min ? arr(0) : nullptr;
+        L0.um2[r] = c->cfg.precision != WANDQS_MIXED && c->N >= std::min(c->reg_tile_min, c->top_tile_min) ? arr(0) : nullptr;
         L0.f[r] = arr(0);
     }
     L0.k2 = arr(0);
@@ -555,7 +556,7 @@ size_t wq::carve_solver(wandqs_ctx* c, char* base) {
     for (int k = 0; k < 2; ++k) c->fields[k] = arr(0);
     for (int r = 0; r < 2; ++r) {
         L0.um[r] = arr(0);
-        L0.um2[r] = c->N >= c->reg_tile_min ? arr(0) : nullptr;
+        L0.um2[r] = c->cfg.precision != WANDQS_MIXED && c->N >= std::min(c->reg_tile_min, c->top_tile_min) ? arr(0) : nullptr;
         L0.f[r] = arr(0);
     }
     L0.k2 = arr(0);

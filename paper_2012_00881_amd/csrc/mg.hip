@@ -933,7 +933,7 @@ struct FuseArgs {
     E* u_out[2];        // smoothed iterate of this pass's down part
     E* f_c[2];          // restricted residual
     double omega;
-    double* norm_part;  // [3R][nblk]: sums r^2, f^2, u^2 of the up part's result
+    double* norm_part;  // [3R][nblk]: sums r^2, f^2, u^2 of the up part's result (or null)
     int nblk;
 };
 
@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(64 * NW) void k_mg_updown_reg(FuseArgs<E> a) {
     __syncthreads();
     xc.get(buf, up, dn, w, lane);
     buf ^= 1;
-    {
+    if (a.norm_part) {
         E rr[R][K][2];
         reg_residual<E, R, K>(rr, u, f, D, dom, up, dn, ih2);
         double acc[3 * R];
@@ -2004,9 +2004,15 @@ struct PassGeom {
     int TX, TY;
     dim3 grid;
 };
+// The finest level takes register tiles from top_tile_min up already in FP64:
+// its up pass then records the norms of the result and fuses with the next
+// cycle's down pass (fuse_shape).
+bool top_tiles(const wandqs_ctx* c) {
+    return c->N >= c->top_tile_min && c->cfg.precision != WANDQS_MIXED;
+}
 PassGeom pass_geom(const wandqs_ctx* c, int N, int nu, bool down, bool norm = false) {
     PassGeom g{};
-    g.reg = N >= c->reg_tile_min;
+    g.reg = N >= c->reg_tile_min || (N == c->N && top_tiles(c));
     g.split = c->reg_split;
     g.split_lds = c->lds_split;
     if (g.reg) {
@@ -2087,40 +2093,52 @@ const char* type_name(float) { return "float"; }
 // right-hand side per workgroup, equal pre- and post-sweep counts of 1 or 2.
 bool fuse_possible(const wandqs_ctx* c) {
     const int nu = c->cfg.nu_pre;
-    return c->mg_fuse && c->lc > 0 && c->N >= c->reg_tile_min && c->reg_split &&
+    return c->mg_fuse && c->lc > 0 && (c->N >= c->reg_tile_min || top_tiles(c)) && c->reg_split &&
            nu == c->cfg.nu_post && nu >= 1 && nu <= 2 && c->lev[0].um2[0] != nullptr;
 }
-#ifndef WQ_FUSE_ROWS
-#define WQ_FUSE_ROWS 8
-#endif
-constexpr int kFuseRows = WQ_FUSE_ROWS;  // rows per wavefront of the fused tiles
-#ifndef WQ_FUSE_WAVES
-#define WQ_FUSE_WAVES 8
-#endif
-constexpr int kFuseWaves = WQ_FUSE_WAVES;  // wavefronts of a fused tile
+// Wavefronts and rows per wavefront of a fused tile (its halo: 10 rows on either
+// side at two sweeps).  At 1024^2 (one right-hand side a workgroup, 2 in all)
+// 8 x 8 took 30 us, 12 x 4 34, 8 x 4 51: the halo's share counts.  At 512^2 8 x 8
+// leaves half the chip idle: 13.7 us, 12 x 4 11.3, 8 x 4 16.0.  At 256^2 the time
+// of one tile counts: 8 x 8 13.1, 12 x 4 10.6, 8 x 4 9.2 (separate passes 13.1,
+// and 4.3 for the residual norms of the result).
+struct FuseShape {
+    int waves, rows;
+};
+FuseShape fuse_shape(int N) {
+    return N >= 1024 ? FuseShape{8, 8} : N >= 512 ? FuseShape{12, 4} : FuseShape{8, 4};
+}
 dim3 fuse_grid(const wandqs_ctx* c, int R) {
+    const FuseShape f = fuse_shape(c->N);
     const int hl = 4 * c->cfg.nu_pre + 2;
-    const int TX = 128 - 2 * hl, TY = kFuseRows * kFuseWaves - 2 * hl, N = c->N;
+    const int TX = 128 - 2 * hl, TY = f.rows * f.waves - 2 * hl, N = c->N;
     return dim3((N + TX - 1) / TX, (N + TY - 1) / TY, R);
+}
+template <int NW, int K>
+void launch_updown_shape(const FuseArgs<double>& a, bool helm, int nu, dim3 grid, hipStream_t s,
+                         const ProfScope& ps) {
+    const dim3 blk(64 * NW);
+    if (helm) {
+        if (nu == 1) WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, true, 1, 1, NW, K>), grid, blk, 0, s, a);
+        else WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, true, 2, 2, NW, K>), grid, blk, 0, s, a);
+    } else {
+        if (nu == 1) WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, false, 1, 1, NW, K>), grid, blk, 0, s, a);
+        else WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, false, 2, 2, NW, K>), grid, blk, 0, s, a);
+    }
 }
 void launch_updown_reg(const FuseArgs<double>& a, bool helm, int nu, dim3 grid, hipStream_t s,
                        const ProfScope& ps) {
-    constexpr int NW = kFuseWaves;
-    const dim3 blk(64 * NW);
-    if (helm) {
-        if (nu == 1) WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, true, 1, 1, NW, kFuseRows>), grid, blk, 0, s, a);
-        else WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, true, 2, 2, NW, kFuseRows>), grid, blk, 0, s, a);
-    } else {
-        if (nu == 1) WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, false, 1, 1, NW, kFuseRows>), grid, blk, 0, s, a);
-        else WQ_KLAUNCH(ps, (k_mg_updown_reg<double, 1, false, 2, 2, NW, kFuseRows>), grid, blk, 0, s, a);
-    }
+    const FuseShape f = fuse_shape(a.N);
+    if (f.rows == 8) launch_updown_shape<8, 8>(a, helm, nu, grid, s, ps);
+    else if (f.waves == 12) launch_updown_shape<12, 4>(a, helm, nu, grid, s, ps);
+    else launch_updown_shape<8, 4>(a, helm, nu, grid, s, ps);
 }
 
 // Level-0 fusion state of one cycle inside a batch (FP64 only).
 struct FuseCtl {
     bool skip_down0 = false;  // the level-0 down pass ran fused into the previous cycle
     bool fuse_up0 = false;    // the level-0 up pass fuses with the next cycle's down pass
-    int next_slot = -1;       // norm slot of the next cycle's incoming iterate
+    int next_slot = -1;       // norm slot of the next cycle's incoming iterate (-1: none)
     int cur = 0;              // level-0 pre-smoothed iterate in um (0) or um2 (1)
 };
 
@@ -2328,12 +2346,13 @@ void vcycle(wandqs_ctx* c, int R, bool helm, const Hier<E>& hz, bool zero_guess,
                 a.k2 = helm ? K(0) : nullptr;
                 const dim3 g = fuse_grid(c, R);
                 a.nblk = g.x * g.y;
-                a.norm_part = c->norm_part + (size_t)fz->next_slot * kNormVec * c->max_tiles;
+                if (fz->next_slot >= 0)
+                    a.norm_part = c->norm_part + (size_t)fz->next_slot * kNormVec * c->max_tiles;
                 const double nodes = (double)L.N * L.N;
                 char nm[64];
                 prof_name(c, nm, sizeof nm, "k_mg_updown_reg<double, 1, %s, %d, %d, %d, %d>@%d",
-                          helm ? "true" : "false", c->cfg.nu_pre, c->cfg.nu_post, kFuseWaves,
-                          kFuseRows, L.N);
+                          helm ? "true" : "false", c->cfg.nu_pre, c->cfg.nu_post, fuse_shape(L.N).waves,
+                          fuse_shape(L.N).rows, L.N);
                 // per owned node and right-hand side: smoothed u, 1/4 coarse e,
                 // f, new smoothed u, 1/4 coarse f; k2 once
                 ProfScope ps(c, nm, nodes * (R * (8.0 + 2.0 + 8.0 + 8.0 + 2.0) + (helm ? 8.0 : 0.0)));
@@ -2417,7 +2436,11 @@ void mixed_iteration(wandqs_ctx* c, int R, bool helm, const Hier<double>& hz, in
 
 }  // namespace
 
+#ifndef WQ_TOP_TILE_MIN
+#define WQ_TOP_TILE_MIN 128
+#endif
 int reg_tile_min_default() { return WQ_REG_TILE_MIN; }
+int top_tile_min_default() { return WQ_TOP_TILE_MIN; }
 int small_tile_max_default() { return WQ_SMALL_TILE_MAX; }
 
 wandqs_status make_dst_tables(wandqs_ctx* c) {
@@ -2578,7 +2601,15 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     const int maxc = c->cfg.mg_max_cycles;
     if (!(c->cfg.mg_rtol > 0.0)) {
         if (whole) whole_cycles(c, R, helm, hz, maxc, inner, -1);
-        else for (int k = 0; k < maxc; ++k) cycle(mixed ? 0 : -1, -1, FuseCtl{});
+        const bool fuse = !mixed && fuse_possible(c);
+        for (int k = 0, cur = 0; k < maxc && !whole; ++k) {
+            FuseCtl fz;
+            fz.skip_down0 = fuse && k > 0;
+            fz.fuse_up0 = fuse && k < maxc - 1;
+            fz.cur = cur;
+            cycle(mixed ? 0 : -1, -1, fz);
+            if (fz.fuse_up0) cur ^= 1;
+        }
         if (graph_check() != WANDQS_OK) return WANDQS_E_HIP;
         WQ_LAUNCH_CHECK();
         if (res) *res = SolveResult{maxc, {-1.0, -1.0}};

@@ -214,6 +214,7 @@ struct wandqs_ctx {
     // levels N >= reg_tile_min run the register-tile pass kernels (environment
     // WANDQS_MG_TILES=lds at init: never; the LDS tiles give the same bits)
     int reg_tile_min = 0;
+    int top_tile_min = 0;  // the same for the finest level of an FP64 solve
     // the tile kernels run the two right-hand sides of a solve as separate
     // workgroups of one launch (environment WANDQS_MG_SPLIT at init: 0, both in
     // every workgroup; reg, split on the register-tile levels only; lds, on the
@@ -373,6 +374,7 @@ const char* setup_solver_ctx(wandqs_ctx* c, const wandqs_config* cfg);
 void set_call_error(const char* m);
 // smallest level that runs the register-tile pass kernels by default
 int reg_tile_min_default();
+int top_tile_min_default();
 // largest level with 16 x 16 LDS tiles by default
 int small_tile_max_default();
 // tables of the exact coarse-level Poisson solves (the 64^2 level and, when
