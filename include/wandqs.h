@@ -314,7 +314,7 @@ wandqs_status wandqs_time_step(wandqs_ctx* ctx, double dt, int32_t n_slices,
  * holds the initial guess and receives the solution.  Uses the context's
  * mg_* settings; h_cycles / h_rel (host, may be NULL) receive the V-cycle count
  * and ||r||/||f|| per rhs.  Poisson solves in the tolerance mode (mg_rtol > 0)
- * with mg_max_cycles >= 16 on grids of 128^2 .. 2048^2 iterate u += L_h^-1 (f -
+ * with mg_max_cycles >= 16 on grids up to 2048^2 iterate u += L_h^-1 (f -
  * L_h u) with an exact FP64 sine-transform solve of the finest grid instead of
  * V-cycles, to the same stop rule; an iteration then counts as a cycle.  Clobbers the context's multigrid scratch arrays and
  * the stored fields used as initial guesses. */

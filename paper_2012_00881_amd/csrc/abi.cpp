@@ -370,8 +370,9 @@ void carve_dst(wandqs_ctx* c, Take&& take, bool top) {
     const bool mixed = c->cfg.precision == WANDQS_MIXED;
     c->dst_S = (float*)take(sizeof(float) * 64 * 64);
     c->dst_M = (float*)take(sizeof(float) * 64 * 64);
-    c->dst_S64 = mixed ? (double*)take(sizeof(double) * 64 * 64) : nullptr;
-    c->dst_M64 = mixed ? (double*)take(sizeof(double) * 64 * 64) : nullptr;
+    const bool in64 = mixed || (top && c->lc == 0);
+    c->dst_S64 = in64 ? (double*)take(sizeof(double) * 64 * 64) : nullptr;
+    c->dst_M64 = in64 ? (double*)take(sizeof(double) * 64 * 64) : nullptr;
     top = top && wq::fst_top_used(c);
     if (top || wq::fst_used(c)) {
         const size_t n = c->lev[top ? 0 : 1].N, one = (n - 1) * (n + 8);

@@ -1273,8 +1273,17 @@ __device__ __forceinline__ void coarse_prolong(C (&uR)[NP], C (&uB)[NP], const C
     }
 }
 
+// The Helmholtz V-cycles of larger grids end on the level of 8 cells with
+// over-relaxed sweeps in place of two more levels: with omega >= 2 / (1 + sin(pi
+// / 8)) = 1.446, the optimum for k2 = 0, a sweep contracts by omega - 1 at least,
+// four by 0.04, less than a V-cycle leaves.  One coarse launch (two cycles) 14.3
+// instead of 15.7 us with the same number of V-cycles.  Poisson V-cycles keep the
+// exact 2-cell level: with four sweeps instead they took twice as many.
+constexpr int kBottomN = 8, kBottomSweeps = 4;
+constexpr double kBottomOmega = 1.45;
+
 // A level of n <= 32 cells in the calling wavefront.
-template <typename C, int n>
+template <typename C, int n, bool HELM>
 struct CoarseWave {
     using L = CoarseLevel<n>;
     static constexpr int NP = L::NP, G = L::G;
@@ -1331,6 +1340,17 @@ struct CoarseWave {
     __device__ __forceinline__ void cycle(C (&uR)[NP], C (&uB)[NP], const C (&fR)[NP], const C (&fB)[NP],
                                           int nu1, int nu2, double omega, double h2max, double k2_two) const {
         constexpr int nc = n / 2;
+        if constexpr (HELM && n == kBottomN) {
+            C iR[NP], iB[NP];
+            table(lds.id, 0, iR);
+            table(lds.id, 1, iB);
+#pragma unroll
+            for (int s = 0; s < kBottomSweeps; ++s) {
+                coarse_half<C, NP>(uR, fR, iR, uB, edge(uB, p), p, h2, C(kBottomOmega));
+                coarse_half<C, NP>(uB, fB, iB, uR, edge(uR, !p), !p, h2, C(kBottomOmega));
+            }
+            return;
+        }
         smooth(uR, uB, fR, fB, nu1);
         C rR[NP], rB[NP];
         {
@@ -1360,7 +1380,7 @@ struct CoarseWave {
                     lds.F[coarse_off_F(nc) + J * nc + x / 2] = x > 0 && J > 0 ? v[m] : C(0);
                 }
             wave_sync();
-            const CoarseWave<C, nc> lc(lds, 2.0 * h, omega, h2max);
+            const CoarseWave<C, nc, HELM> lc(lds, 2.0 * h, omega, h2max);
             constexpr int NC = CoarseLevel<nc>::NP;
             C cR[NC], cB[NC], gR[NC], gB[NC];
 #pragma unroll
@@ -1507,7 +1527,7 @@ __global__ __launch_bounds__(coarse_threads<n0>()) void k_mg_coarse(CoarseArgs<E
         if (a.norm_part) norms(cyc);
         for (int k = 0; k < a.inner; ++k) {
             if constexpr (n0 < 64) {
-                const CoarseWave<C, n0> top(lds, a.h, a.omega, a.h2max);
+                const CoarseWave<C, n0, false> top(lds, a.h, a.omega, a.h2max);
                 top.cycle(uR, uB, fR, fB, a.nu1, a.nu2, a.omega, a.h2max, k2_two);
             } else {
                 smooth(a.nu1);
@@ -1525,7 +1545,7 @@ __global__ __launch_bounds__(coarse_threads<n0>()) void k_mg_coarse(CoarseArgs<E
                     }
                 __syncthreads();
                 if (w == 0) {
-                    const CoarseWave<C, 32> lc(lds, 2.0 * a.h, a.omega, a.h2max);
+                    const CoarseWave<C, 32, HELM> lc(lds, 2.0 * a.h, a.omega, a.h2max);
                     constexpr int NC = CoarseLevel<32>::NP;
                     C cR[NC], cB[NC], gR[NC], gB[NC];
 #pragma unroll
@@ -1737,16 +1757,118 @@ __global__ __launch_bounds__(1024) void k_coarse_dst64(DstArgs64<E> a) {
     }
 }
 
+// Whole Poisson solves on grids of n^2 <= 64^2 in one workgroup per right-hand
+// side: `iters` iterations u += L_h^-1 (f - L_h u), the exact solve by the four
+// products of k_coarse_dst64 (the tables of a smaller grid are padded with
+// zeros), and the norms of every iterate.  A thread keeps f and u of the four
+// nodes of its product tile in registers; u's neighbours come through LDS.
+// Bound by the chain of four products and two residuals of one workgroup: 21 us
+// for one iteration (what a slice's guess needs) where 5 V-cycles took 58; 16 of
+// these solves in 8 slices at 64^2: 2.83 -> 1.82 ms.
+struct Poisson64Args {
+    int n, pitch;
+    double ih2;
+    const double* f[2];
+    double* u[2];
+    const double* S;
+    const double* M;
+    int iters;
+    double* norm_part;  // the sums of r^2, f^2, u^2 before each iteration and after the last
+    size_t norm_stride;
+};
+
+__global__ __launch_bounds__(1024) void k_poisson64(Poisson64Args a) {
+    __shared__ double sS[kDstN * kDstLd64];
+    __shared__ double sX[kDstN * kDstLd64];
+    __shared__ double sY[kDstN * kDstLd64];
+    __shared__ double red[16][3];
+    const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int i0 = 16 * (w >> 2), j0 = 16 * (w & 3);
+    const int ti = i0 + 4 * (lane >> 4), tj = j0 + (lane & 15);  // node (x, y) = (tj + 1, ti + q + 1)
+    const int last = a.n - 2;                                    // the last interior index
+    double mv[4], f[4], u[4];
+    {
+        double sv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool in = tj <= last && ti + q <= last;
+            const size_t g = in ? (size_t)(ti + q + 1) * a.pitch + tj + 1 : 0;
+            mv[q] = a.M[(ti + q) * kDstN + tj];
+            sv[q] = a.S[tid + q * 1024];
+            f[q] = a.f[r][g] * (in ? 1.0 : 0.0);
+            u[q] = a.u[r][g] * (in ? 1.0 : 0.0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = tid + q * 1024;
+            sS[(i >> 6) * kDstLd64 + (i & 63)] = sv[q];
+        }
+    }
+    for (int it = 0;; ++it) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sY[(ti + q) * kDstLd64 + tj] = u[q];
+        __syncthreads();
+        double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int y = ti + q, i = y * kDstLd64 + tj;
+            const bool in = tj <= last && y <= last;
+            const double l = tj > 0 ? sY[i - 1] : 0.0, h = tj < last ? sY[i + 1] : 0.0;
+            const double d = y > 0 ? sY[i - kDstLd64] : 0.0, t = y < last ? sY[i + kDstLd64] : 0.0;
+            const double v = in ? f[q] - (l + h + d + t - 4.0 * u[q]) * a.ih2 : 0.0;
+            sX[tj * kDstLd64 + y] = v;
+            s[0] += v * v;
+            s[1] += f[q] * f[q];
+            s[2] += u[q] * u[q];
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], d, 64);
+        if (lane == 0)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) red[w][q] = s[q];
+        __syncthreads();
+        if (tid < 3) {
+            double t = 0.0;
+            for (int k = 0; k < 16; ++k) t += red[k][tid];
+            a.norm_part[it * a.norm_stride + 3 * r + tid] = t;
+        }
+        if (it == a.iters) break;
+        dst_v4d d = tile64<kDstN, kDstLd64, kDstLd64>(sS + i0 * kDstLd64, sX, j0);  // Y = S F
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sY[(ti + q) * kDstLd64 + tj] = d[q];
+        __syncthreads();
+        d = tile64<kDstN, kDstLd64, kDstLd64>(sY + i0 * kDstLd64, sS, j0);  // X = M o (Y S), stored transposed
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sX[tj * kDstLd64 + ti + q] = mv[q] * d[q];
+        __syncthreads();
+        d = tile64<kDstN, kDstLd64, kDstLd64>(sS + i0 * kDstLd64, sX, j0);  // Y = S X
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sY[(ti + q) * kDstLd64 + tj] = d[q];
+        __syncthreads();
+        d = tile64<kDstN, kDstLd64, kDstLd64>(sY + i0 * kDstLd64, sS, j0);  // U = Y S
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] += d[q];
+        __syncthreads();  // every read of sY and red is done before they are rewritten
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (tj <= last && ti + q <= last) a.u[r][(size_t)(ti + q + 1) * a.pitch + tj + 1] = u[q];
+}
+
 // Tables of the exact coarse Poisson solve on an n^2 level of spacing H:
 // S_jk = sin(pi (j+1)(k+1) / n) (the argument reduced exactly modulo 2 pi),
 // M_jk = 1 / ((n/2)^2 lambda_jk), lambda_jk = -(4/H^2)(sin^2(pi (j+1)/2n) +
 // sin^2(pi (k+1)/2n)), the eigenvalue of the 5-point operator for the sine
-// mode (j+1, k+1); row and column n-1 are zero.  Float and (when S64 is set)
-// double copies.
+// mode (j+1, k+1); the rows and columns from n-1 on are zero (n <= 64 = the
+// tables' stride).  Float and (when S64 is set) double copies.
 __global__ void k_dst_tables(int n, double H, float* S, float* M, double* S64, double* M64) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * n) return;
-    const int jj = i / n, kk = i - jj * n;
+    if (i >= kDstN * kDstN) return;
+    const int jj = i / kDstN, kk = i - jj * kDstN;
     const bool in = jj < n - 1 && kk < n - 1;
     const double pi = 3.14159265358979323846;
     double sv = 0.0, mv = 0.0;
@@ -2209,6 +2331,28 @@ void whole_cycles(wandqs_ctx* c, int R, bool helm, const Hier<double>& hz, int n
 #undef WQ_WHOLE
 }
 
+// `iters` iterations with the exact solve on a grid of at most 64^2, in one launch;
+// the norms go to the slots from `slot` on, as in whole_cycles.
+void whole_direct(wandqs_ctx* c, int R, const Hier<double>& hz, int iters, int slot) {
+    const wq::Level& L = c->lev[0];
+    Poisson64Args a{};
+    a.n = L.N;
+    a.pitch = L.pitch;
+    a.ih2 = 1.0 / (L.h * L.h);
+    for (int r = 0; r < R; ++r) {
+        a.f[r] = hz.f0[r];
+        a.u[r] = hz.u0[r];
+    }
+    a.S = c->dst_S64;
+    a.M = c->dst_M64;
+    a.iters = iters;
+    a.norm_stride = (size_t)kNormVec * c->max_tiles;
+    a.norm_part = c->norm_part + slot * a.norm_stride;
+    const double nodes = (double)(c->N + 1) * (c->N + 1);
+    ProfScope ps(c, "k_poisson64", nodes * 24.0 * R + 2.0 * 8.0 * kDstN * kDstN);
+    WQ_KLAUNCH(ps, k_poisson64, dim3(R), dim3(1024), 0, c->stream, a);
+}
+
 // One V-cycle on levels 0..L (grids above 64^2).  zero_guess: the level-0 iterate starts from 0.
 // norm_slot >= 0 (double only) records the residual of the incoming iterate.
 template <typename E>
@@ -2444,9 +2588,8 @@ int top_tile_min_default() { return WQ_TOP_TILE_MIN; }
 int small_tile_max_default() { return WQ_SMALL_TILE_MAX; }
 
 wandqs_status make_dst_tables(wandqs_ctx* c) {
-    const int n1 = kDstN;
-    hipLaunchKernelGGL(k_dst_tables, dim3((n1 * n1 + 255) / 256), dim3(256), 0, c->stream, n1,
-                       c->lev[c->lc].h, c->dst_S, c->dst_M, c->dst_S64, c->dst_M64);
+    hipLaunchKernelGGL(k_dst_tables, dim3(kDstN * kDstN / 256), dim3(256), 0, c->stream,
+                       c->lev[c->lc].N, c->lev[c->lc].h, c->dst_S, c->dst_M, c->dst_S64, c->dst_M64);
     WQ_LAUNCH_CHECK();
     return make_fst_tables(c);
 }
@@ -2510,9 +2653,9 @@ wandqs_status wait_published(wandqs_ctx* c, const uint32_t* h_seq, uint32_t seq)
     return WANDQS_E_HIP;
 }
 
-// Poisson solves in tolerance mode on grids of 128^2 .. 2048^2 iterate
+// Poisson solves in tolerance mode on grids up to 2048^2 iterate
 // u += L_h^-1 (f - L_h u) with the exact sine-transform solve on the finest
-// level itself (fst.hip) in FP64, in both precision forms: the correction's
+// level itself (fst.hip; up to 64^2 k_poisson64) in FP64, in both precision forms: the correction's
 // rounding (1e-14 .. 3e-13 of it) is the only error an iteration leaves, so from
 // an extrapolated guess one iteration reaches the rounding floor and from zero
 // two do, where the V-cycles that end with the same solve one level down took 5
@@ -2526,7 +2669,7 @@ wandqs_status wait_published(wandqs_ctx* c, const uint32_t* h_seq, uint32_t seq)
 constexpr int kDirectMinCycles = 16;
 bool direct_poisson(const wandqs_ctx* c, bool helm) {
     return !helm && c->cfg.mg_rtol > 0.0 && c->cfg.mg_max_cycles >= kDirectMinCycles &&
-           c->fst_top_tw != nullptr;
+           (c->fst_top_tw != nullptr || c->lc == 0);
 }
 
 // Solve with the context's stop rule.  Tolerance mode (mg_rtol > 0) runs a batch
@@ -2642,7 +2785,8 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     while (true) {
         int b = done == 0 ? pred : 1;
         if (done + b > maxc) b = maxc - done;
-        if (whole) whole_cycles(c, R, helm, hz, b, inner, done);
+        if (whole && direct) whole_direct(c, R, hz, b, done);
+        else if (whole) whole_cycles(c, R, helm, hz, b, inner, done);
         for (int k = 0; k < b && !whole; ++k) {
             const int cyc = done + k;
             FuseCtl fz;
