@@ -7,8 +7,8 @@
 // histogram (integer atomics), exclusive scan, scatter, then each cell's
 // particles are ordered by ID, so the storage order -- and every floating-point
 // sum that follows -- is independent of thread timing.  Deposits are
-// atomics-free: a workgroup owns a tile of nodes, one thread per cell of the
-// tile (plus the one-cell rim shared with the neighbouring tiles) sums its
+// atomics-free: a workgroup owns a tile of nodes, two or four lanes per cell of the
+// tile (plus the one-cell rim shared with the neighbouring tiles) sum its
 // particles' corner weights in registers, and each node adds its four cells'
 // corners from LDS in a fixed order.
 #include <algorithm>
@@ -237,55 +237,80 @@ __global__ __launch_bounds__(256) void k_cell_sort_big(const int32_t* __restrict
     }
 }
 
-// particles per batch of loads in the deposits (latencies overlap; the sums
-// keep the cell's particle order), one thread per cell of a tile's
-// (tile + 1)^2 cells.  The density deposit uses kDepTile = 16 (five
-// wavefronts); the current and stress deposit, whose LDS sets the occupancy,
-// 15 x 15 node tiles (16 x 16 cells, four wavefronts: the fastest measured of
-// 8..16).
-constexpr int kDepBatch = 8, kDepBatchJ = 4;
-#ifndef WQ_DEP_TILE_J
-#define WQ_DEP_TILE_J 15
-#endif
-#ifndef WQ_DEP_THREADS_J
-#define WQ_DEP_THREADS_J 256
-#endif
-constexpr int kDepThreads = 320, kDepTileJ = WQ_DEP_TILE_J, kDepThreadsJ = WQ_DEP_THREADS_J;
-static_assert((kDepTile + 1) * (kDepTile + 1) <= kDepThreads, "one cell per deposit thread");
+// The deposits.  A workgroup owns a tile of 15 x 15 nodes: LANES lanes per cell of
+// the tile and its rim (16 x 16 cells), lane q of a cell takes its particles q,
+// q + LANES, ... (in batches of loads whose latencies overlap) and the lanes'
+// sums are joined in a fixed order, each lane ending with its share of the cell's
+// corners.  Bound by latency where cells hold many particles (the sheath of a
+// blowout) and by the loads elsewhere, which neighbouring lanes coalesce.  One
+// lane per cell took (n*, then j and T) 11.3 / 17.8 us at 256^2 with 4 particles
+// per lattice cell, 32 / 66 at 1024^2, 39 / 64 at 512^2 with 9; now 8.0 / 14.0,
+// 28 / 59 and 19 / 40.
+constexpr int kDepTileP = 15, kDepCells = kDepTileP + 1;
+template <int LANES> constexpr int dep_threads_n() { return LANES * kDepCells * kDepCells; }
+constexpr int kDepThreadsJ = 512;  // (its registers: 1024 leave one workgroup per CU, 45 us for the 40)
+constexpr int kDepBatch = 4, kDepBatchJ = 2;
+
+// The value of the quad's lane q ^ X (X = 1 or 2), by DPP.
+template <int X>
+__device__ __forceinline__ double quad_xor(double v) {
+    constexpr int ctrl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1, 0, 3, 2], [2, 3, 0, 1]
+    const unsigned long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, ctrl, 0xF, 0xF, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), ctrl, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// Joins the corner values s[4] of a cell's LANES lanes in a fixed order; lane q
+// puts the corners that it ends with at out[corner * stride].
+template <int LANES>
+__device__ __forceinline__ void join_corners(double s0, double s1, double s2, double s3, int q, double* out,
+                                             int stride) {
+    static_assert(LANES == 2 || LANES == 4, "lanes per cell");
+    const bool b0 = q & 1, b1 = q & 2;
+    const double lo = (b0 ? s1 : s0) + quad_xor<1>(b0 ? s0 : s1);  // corner b0 of lanes q, q ^ 1
+    const double hi = (b0 ? s3 : s2) + quad_xor<1>(b0 ? s2 : s3);  // corner 2 + b0
+    if constexpr (LANES == 2) {
+        out[q * stride] = lo;
+        out[(2 + q) * stride] = hi;
+    } else {
+        out[q * stride] = (b1 ? hi : lo) + quad_xor<2>(b1 ? lo : hi);
+    }
+}
 
 // n* = deposit(1) (Sec. III.B: surface density) and the psi right-hand side
 // n* - n0 (eq. (12)) on the interior nodes.
-template <int TN>
-__global__ __launch_bounds__(kDepThreads) void k_deposit_n(int N, double L, double h, double wdep,
+template <int LANES>
+__global__ __launch_bounds__(dep_threads_n<LANES>()) void k_deposit_n(int N, double L, double h, double wdep,
                                                    double n0, int pitch,
                                                    const double* __restrict__ x,
                                                    const double* __restrict__ y,
                                                    const int32_t* __restrict__ start,
                                                    double* __restrict__ nstar,
                                                    double* __restrict__ fpsi) {
-    constexpr int TC = TN + 1;
+    constexpr int TC = kDepCells, TN = kDepTileP, kT = dep_threads_n<LANES>(), kB = kDepBatch;
     __shared__ double corner[TC * TC][4];
     int tbx, tby;
     tile_of_block(tbx, tby);
     const int a0 = tbx * TN, b0 = tby * TN;
-    for (int c = threadIdx.x; c < TC * TC; c += blockDim.x) {
+    for (int i = threadIdx.x; i < LANES * TC * TC; i += kT) {
+        const int c = i / LANES, q = i % LANES;
         const int cy = c / TC, cx = c - cy * TC;
         const int ga = a0 - 1 + cx, gb = b0 - 1 + cy;
         double s00 = 0.0, s10 = 0.0, s01 = 0.0, s11 = 0.0;
         if (ga >= 0 && ga < N && gb >= 0 && gb < N) {
             const int cell = gb * N + ga;
             const int k1 = start[cell + 1];
-            // the cell's particles in order, loaded kDepBatch at a time
-            for (int k0 = start[cell]; k0 < k1; k0 += kDepBatch) {
-                double xv[kDepBatch], yv[kDepBatch];
+            for (int k0 = start[cell] + q; k0 < k1; k0 += LANES * kB) {
+                double xv[kB], yv[kB];
 #pragma unroll
-                for (int t = 0; t < kDepBatch; ++t) {
-                    xv[t] = k0 + t < k1 ? x[k0 + t] : 0.0;
-                    yv[t] = k0 + t < k1 ? y[k0 + t] : 0.0;
+                for (int t = 0; t < kB; ++t) {
+                    const int k = min(k0 + LANES * t, k1 - 1);
+                    xv[t] = x[k];
+                    yv[t] = y[k];
                 }
 #pragma unroll
-                for (int t = 0; t < kDepBatch; ++t) {
-                    if (k0 + t >= k1) break;
+                for (int t = 0; t < kB; ++t) {
+                    if (k0 + LANES * t >= k1) break;
                     const double dx = (xv[t] + L) / h - ga;
                     const double dy = (yv[t] + L) / h - gb;
                     s00 += (1.0 - dx) * (1.0 - dy);
@@ -295,13 +320,10 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit_n(int N, double L, doub
                 }
             }
         }
-        corner[c][0] = s00;
-        corner[c][1] = s10;
-        corner[c][2] = s01;
-        corner[c][3] = s11;
+        join_corners<LANES>(s00, s10, s01, s11, q, corner[c], 1);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < TN * TN; i += blockDim.x) {
+    for (int i = threadIdx.x; i < TN * TN; i += kT) {
         const int ny = i / TN, nx = i - ny * TN;
         const int ga = a0 + nx, gb = b0 + ny;
         if (ga > N || gb > N) continue;
@@ -320,7 +342,7 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit_n(int N, double L, doub
 // Gather psi to each particle: g_i = 1 + psi_i (> 0 or the NONPHYS flag),
 // V_i = p_i / g_i (eq. (6)); deposit j = n*<V> (eq. (9)) and T = n*<V V>
 // (below eq. (16)).  Output order: jx, jy, Txx, Txy, Tyy.
-template <int TN>
+template <int LANES>
 __global__ __launch_bounds__(kDepThreadsJ) void k_deposit_jT(int N, double L, double h, double wdep,
                                                     int pitch, const double* __restrict__ x,
                                                     const double* __restrict__ y,
@@ -334,14 +356,15 @@ __global__ __launch_bounds__(kDepThreadsJ) void k_deposit_jT(int N, double L, do
                                                     double* __restrict__ txy,
                                                     double* __restrict__ tyy,
                                                     int32_t* __restrict__ flags) {
-    constexpr int TC = TN + 1;
+    constexpr int TC = kDepCells, TN = kDepTileP, kT = kDepThreadsJ, kB = kDepBatchJ;
     constexpr int M = 5;
     __shared__ double corner[TC * TC][4 * M];
     int tbx, tby;
     tile_of_block(tbx, tby);
     const int a0 = tbx * TN, b0 = tby * TN;
     bool bad = false;
-    for (int c = threadIdx.x; c < TC * TC; c += blockDim.x) {
+    for (int i = threadIdx.x; i < LANES * TC * TC; i += kT) {
+        const int c = i / LANES, l = i % LANES;
         const int cy = c / TC, cx = c - cy * TC;
         const int ga = a0 - 1 + cx, gb = b0 - 1 + cy;
         double s[4][M];
@@ -355,20 +378,19 @@ __global__ __launch_bounds__(kDepThreadsJ) void k_deposit_jT(int N, double L, do
             const double p00 = psi[g], p10 = psi[g + 1], p01 = psi[g + pitch],
                          p11 = psi[g + pitch + 1];
             const int k1 = start[cell + 1];
-            // the cell's particles in order, loaded kDepBatchJ at a time
-            for (int k0 = start[cell]; k0 < k1; k0 += kDepBatchJ) {
-                double xv[kDepBatchJ], yv[kDepBatchJ], pxv[kDepBatchJ], pyv[kDepBatchJ];
+            for (int k0 = start[cell] + l; k0 < k1; k0 += LANES * kB) {
+                double xv[kB], yv[kB], pxv[kB], pyv[kB];
 #pragma unroll
-                for (int t = 0; t < kDepBatchJ; ++t) {
-                    const bool in = k0 + t < k1;
-                    xv[t] = in ? x[k0 + t] : 0.0;
-                    yv[t] = in ? y[k0 + t] : 0.0;
-                    pxv[t] = in ? px[k0 + t] : 0.0;
-                    pyv[t] = in ? py[k0 + t] : 0.0;
+                for (int t = 0; t < kB; ++t) {
+                    const int k = min(k0 + LANES * t, k1 - 1);
+                    xv[t] = x[k];
+                    yv[t] = y[k];
+                    pxv[t] = px[k];
+                    pyv[t] = py[k];
                 }
 #pragma unroll
-                for (int t = 0; t < kDepBatchJ; ++t) {
-                    if (k0 + t >= k1) break;
+                for (int t = 0; t < kB; ++t) {
+                    if (k0 + LANES * t >= k1) break;
                     const double dx = (xv[t] + L) / h - ga;
                     const double dy = (yv[t] + L) / h - gb;
                     const double gi = 1.0 + cic_gather(p00, p10, p01, p11, dx, dy);
@@ -386,14 +408,12 @@ __global__ __launch_bounds__(kDepThreadsJ) void k_deposit_jT(int N, double L, do
             }
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int m = 0; m < M; ++m) corner[c][r * M + m] = s[r][m];
+        for (int m = 0; m < M; ++m) join_corners<LANES>(s[0][m], s[1][m], s[2][m], s[3][m], l, corner[c] + m, M);
     }
     if (bad) atomicOr(flags, 1);
     __syncthreads();
     double* out[M] = {jx, jy, txx, txy, tyy};
-    for (int i = threadIdx.x; i < TN * TN; i += blockDim.x) {
+    for (int i = threadIdx.x; i < TN * TN; i += kT) {
         const int ny = i / TN, nx = i - ny * TN;
         const int ga = a0 + nx, gb = b0 + ny;
         if (ga > N || gb > N) continue;
@@ -776,29 +796,42 @@ wandqs_status slice_sort(wandqs_ctx* c) {
     return WANDQS_OK;
 }
 
+// Lanes per cell of the deposits by the lattice's particles per cell: with 9 four
+// lanes take 19 / 40 us (512^2, n* / j and T), two 24 / 59; with 4 four take 34 /
+// 68 at 1024^2, two 28 / 59; with 1 two 4.5 / 4.3 at 64^2, four 4.1 / 5.7.
+int dep_lanes(const wandqs_ctx* c) { return c->ppc >= 9 ? 4 : 2; }
+
 wandqs_status deposit_n(wandqs_ctx* c) {
-    const int nt = (c->N + 1 + kDepTile - 1) / kDepTile;
+    const int nt = (c->N + 1 + kDepTileP - 1) / kDepTileP;
     const double wdep = c->cfg.n0 / c->ppc;
+    const int lanes = dep_lanes(c);
     {
-        ProfScope ps(c, "k_deposit_n<16>", (double)c->P * 16.0 + (double)c->N * c->N * 4.0 + (double)(c->N + 1) * (c->N + 1) * 16.0);
-        WQ_KLAUNCH(ps, (k_deposit_n<kDepTile>), dim3(nt, nt), dim3(kDepThreads), 0, c->stream, c->N, c->L,
-                           c->h, wdep, c->cfg.n0, c->lev[0].pitch, c->pa[c->cur][0], c->pa[c->cur][1],
-                           c->cell_start, c->mom[0], c->lev[0].f[0]);
+        ProfScope ps(c, "k_deposit_n", (double)c->P * 16.0 + (double)c->N * c->N * 4.0 + (double)(c->N + 1) * (c->N + 1) * 16.0);
+#define WQ_DEP_N(K)                                                                                        \
+    WQ_KLAUNCH(ps, k_deposit_n<K>, dim3(nt, nt), dim3(dep_threads_n<K>()), 0, c->stream, c->N, c->L, c->h, \
+               wdep, c->cfg.n0, c->lev[0].pitch, c->pa[c->cur][0], c->pa[c->cur][1], c->cell_start,        \
+               c->mom[0], c->lev[0].f[0])
+        if (lanes == 4) WQ_DEP_N(4);
+        else WQ_DEP_N(2);
+#undef WQ_DEP_N
     }
     WQ_LAUNCH_CHECK();
     return WANDQS_OK;
 }
 
 wandqs_status deposit_jT(wandqs_ctx* c) {
-    const int nt = (c->N + 1 + kDepTileJ - 1) / kDepTileJ;
+    const int nt = (c->N + 1 + kDepTileP - 1) / kDepTileP;
     const double wdep = c->cfg.n0 / c->ppc;
-    const int k = c->cur;
+    const int k = c->cur, lanes = dep_lanes(c);
     {
-        ProfScope ps(c, "k_deposit_jT<15>", (double)c->P * 32.0 + (double)c->N * c->N * 4.0 + (double)(c->N + 1) * (c->N + 1) * 48.0);
-        WQ_KLAUNCH(ps, (k_deposit_jT<kDepTileJ>), dim3(nt, nt), dim3(kDepThreadsJ), 0, c->stream, c->N, c->L,
-                           c->h, wdep, c->lev[0].pitch, c->pa[k][0], c->pa[k][1], c->pa[k][2],
-                           c->pa[k][3], c->cell_start, c->fields[0], c->mom[1], c->mom[2], c->mom[3],
-                           c->mom[4], c->mom[5], c->flags);
+        ProfScope ps(c, "k_deposit_jT", (double)c->P * 32.0 + (double)c->N * c->N * 4.0 + (double)(c->N + 1) * (c->N + 1) * 48.0);
+#define WQ_DEP_J(K)                                                                                       \
+    WQ_KLAUNCH(ps, k_deposit_jT<K>, dim3(nt, nt), dim3(kDepThreadsJ), 0, c->stream, c->N, c->L, c->h, \
+               wdep, c->lev[0].pitch, c->pa[k][0], c->pa[k][1], c->pa[k][2], c->pa[k][3], c->cell_start,  \
+               c->fields[0], c->mom[1], c->mom[2], c->mom[3], c->mom[4], c->mom[5], c->flags)
+        if (lanes == 4) WQ_DEP_J(4);
+        else WQ_DEP_J(2);
+#undef WQ_DEP_J
     }
     WQ_LAUNCH_CHECK();
     return WANDQS_OK;
