@@ -16,12 +16,13 @@
 //   particle-ID order.
 #include <cmath>
 
+#include "lanes.h"
 #include "wq_common.h"
 
 namespace wq {
 namespace {
 
-constexpr int TN = kDepTile;
+constexpr int TN = 15;  // tile of nodes owned by a workgroup
 constexpr int TC = TN + 1;
 
 __device__ __forceinline__ void cic(double x, double L, double h, int N, int& c, double& d) {
@@ -37,12 +38,12 @@ struct Interp {
     double v, dx, dy;
 };
 __device__ __forceinline__ Interp interp(double f00, double f10, double f01, double f11,
-                                         double ddx, double ddy, double h) {
+                                         double ddx, double ddy, double ih) {
     Interp r;
     r.v = f00 * (1.0 - ddx) * (1.0 - ddy) + f10 * ddx * (1.0 - ddy) + f01 * (1.0 - ddx) * ddy +
           f11 * ddx * ddy;
-    r.dx = ((f10 - f00) * (1.0 - ddy) + (f11 - f01) * ddy) / h;
-    r.dy = ((f01 - f00) * (1.0 - ddx) + (f11 - f10) * ddx) / h;
+    r.dx = ((f10 - f00) * (1.0 - ddy) + (f11 - f01) * ddy) * ih;
+    r.dy = ((f01 - f00) * (1.0 - ddx) + (f11 - f10) * ddx) * ih;
     return r;
 }
 
@@ -60,16 +61,15 @@ __device__ __forceinline__ double grady(const double* psi, int pitch, int N, dou
     return b == 0 ? (pr - pc) / h : (b == N ? (pc - pl) / h : (pr - pl) / (2.0 * h));
 }
 
-// Particles per batch of loads in the reverse push and deposits: a batch's
-// loads (and then its adjoint loads by ID) are all in flight together, the
-// particles then taken in order as before.  Measured over the C5 reverse
-// sweep: 386 / 268 us for k_push_adj / k_dep_adj with 2, 566 / 279 with 4
-// (k_push_adj's registers then allow one wavefront per SIMD), 446 / 450 with
-// the particles loaded one at a time.
-#ifndef WQ_ADJ_BATCH
-#define WQ_ADJ_BATCH 2
-#endif
-constexpr int kAdjBatch = WQ_ADJ_BATCH;
+// The reverse push and deposits take kAdjLanes lanes per cell of a tile's 16 x 16
+// cells, as the forward deposits do, with kAdjBatch particles per lane and batch
+// of loads (then of adjoint loads by ID), all in flight together.  Bound by the
+// latency of those loads at two wavefronts per SIMD (242 and 202 registers): at
+// 256^2 with 4 particles a cell 18.2 us for k_push_adj and 15.6 for k_dep_adj;
+// 256 threads 24.2 / 18.8, four lanes and batches of one 25.4 / 15.3.  With one
+// lane per cell, 17 x 17 cells on 256 threads (a second trip for 33 of them) and
+// a division per quotient they took 62.8 and 40.2.
+constexpr int kAdjBatch = 2, kAdjLanes = 2, kAdjThreads = kAdjLanes * TC * TC;
 
 __device__ __forceinline__ bool interior(int N, int a, int b) {
     return a >= 1 && b >= 1 && a <= N - 1 && b <= N - 1;
@@ -111,7 +111,8 @@ struct PushAdjArgs {
 // forward took is differentiated).  A workgroup owns the cells of its tile and
 // writes their particles; the rim cells below and left of the tile only add to
 // the corner sums of the tile's nodes.
-__global__ __launch_bounds__(256) void k_push_adj(PushAdjArgs a) {
+template <int LANES>
+__global__ __launch_bounds__(kAdjThreads) void k_push_adj(PushAdjArgs a) {
     constexpr int M = 5;
     __shared__ double corner[TC * TC][4 * M];
     int tbx, tby;
@@ -120,7 +121,9 @@ __global__ __launch_bounds__(256) void k_push_adj(PushAdjArgs a) {
     const int N = a.N, pitch = a.pitch;
     const double h = a.h, L = a.L, d = a.st[1];
     const int64_t P = a.P;
-    for (int c = threadIdx.x; c < TC * TC; c += blockDim.x) {
+    const double ih = 1.0 / h;
+    for (int i = threadIdx.x; i < LANES * TC * TC; i += kAdjThreads) {
+        const int c = i / LANES, l = i % LANES;
         const int cy = c / TC, cx = c - cy * TC;
         const int ga = a0 - 1 + cx, gb = b0 - 1 + cy;
         double s[4][M];
@@ -153,13 +156,12 @@ __global__ __launch_bounds__(256) void k_push_adj(PushAdjArgs a) {
             const double bz00 = a.Bz[g], bz10 = a.Bz[g + 1], bz01 = a.Bz[g + pitch],
                          bz11 = a.Bz[g + pitch + 1];
             const int k0 = a.start[cell], k1 = k0 + (a.start[cell + 1] - k0) * (valid ? 1 : 0);
-            for (int kb = k0; kb < k1; kb += kAdjBatch) {
-            const int cnt = min(kAdjBatch, k1 - kb);
+            for (int kb = k0 + l; kb < k1; kb += LANES * kAdjBatch) {
             double xv[kAdjBatch], yv[kAdjBatch], pxv[kAdjBatch], pyv[kAdjBatch];
             int64_t idv[kAdjBatch];
 #pragma unroll
             for (int ib = 0; ib < kAdjBatch; ++ib) {
-                const int kk = kb + min(ib, cnt - 1);
+                const int kk = min(kb + LANES * ib, k1 - 1);
                 xv[ib] = a.x[kk];
                 yv[ib] = a.y[kk];
                 pxv[ib] = a.px[kk];
@@ -173,26 +175,26 @@ __global__ __launch_bounds__(256) void k_push_adj(PushAdjArgs a) {
                 for (int q = 0; q < 4; ++q) av[ib][q] = a.adj_in[q * P + idv[ib]];
 #pragma unroll
             for (int ib = 0; ib < kAdjBatch; ++ib) {
-                if (ib >= cnt) break;
-                const int k = kb + ib;
+                const int k = kb + LANES * ib;
+                if (k >= k1) break;
                 const double ddx = (xv[ib] + L) / h - ga, ddy = (yv[ib] + L) / h - gb;
-                const Interp gp = interp(p00, p10, p01, p11, ddx, ddy, h);
-                const Interp Gxi = interp(gx00, gx10, gx01, gx11, ddx, ddy, h);
-                const Interp Gyi = interp(gy00, gy10, gy01, gy11, ddx, ddy, h);
-                const Interp bxi = interp(bx00, bx10, bx01, bx11, ddx, ddy, h);
-                const Interp byi = interp(by00, by10, by01, by11, ddx, ddy, h);
-                const Interp bzi = interp(bz00, bz10, bz01, bz11, ddx, ddy, h);
-                const double G_ = 1.0 + gp.v, p0x = pxv[ib], p0y = pyv[ib];
+                const Interp gp = interp(p00, p10, p01, p11, ddx, ddy, ih);
+                const Interp Gxi = interp(gx00, gx10, gx01, gx11, ddx, ddy, ih);
+                const Interp Gyi = interp(gy00, gy10, gy01, gy11, ddx, ddy, ih);
+                const Interp bxi = interp(bx00, bx10, bx01, bx11, ddx, ddy, ih);
+                const Interp byi = interp(by00, by10, by01, by11, ddx, ddy, ih);
+                const Interp bzi = interp(bz00, bz10, bz01, bz11, ddx, ddy, ih);
+                const double G_ = 1.0 + gp.v, iG = 1.0 / G_, p0x = pxv[ib], p0y = pyv[ib];
                 const double Gx = Gxi.v, Gy = Gyi.v, bx = bxi.v, by = byi.v, bz = bzi.v;
                 // forward replay
-                const double gam = (1.0 + p0x * p0x + p0y * p0y + G_ * G_) / (2.0 * G_);
-                const double Fx = gam * Gx / G_ - by, Fy = gam * Gy / G_ + bx;
+                const double gam = (1.0 + p0x * p0x + p0y * p0y + G_ * G_) * (0.5 * iG);
+                const double Fx = gam * Gx * iG - by, Fy = gam * Gy * iG + bx;
                 const double mx = p0x + 0.5 * d * Fx, my = p0y + 0.5 * d * Fy;
-                const double t = bz * d / (2.0 * G_), sr = 2.0 * t / (1.0 + t * t);
+                const double t = bz * d * (0.5 * iG), it = 1.0 / (1.0 + t * t), sr = 2.0 * t * it;
                 const double qx = mx - t * my, qy = my + t * mx;
                 const double rx = mx - sr * qy, ry = my + sr * qx;
                 const double p1x = rx + 0.5 * d * Fx, p1y = ry + 0.5 * d * Fy;
-                const double x1 = xv[ib] + d * p1x / G_, y1 = yv[ib] + d * p1y / G_;
+                const double x1 = xv[ib] + d * p1x * iG, y1 = yv[ib] + d * p1y * iG;
                 // reverse
                 double x1b = av[ib][0], y1b = av[ib][1];
                 double p1xb = av[ib][2], p1yb = av[ib][3];
@@ -205,9 +207,9 @@ __global__ __launch_bounds__(256) void k_push_adj(PushAdjArgs a) {
                     p1yb = -p1yb;
                 }
                 double xbar = x1b, ybar = y1b;
-                p1xb += x1b * d / G_;
-                p1yb += y1b * d / G_;
-                double gbar = -(x1b * d * p1x + y1b * d * p1y) / (G_ * G_);
+                p1xb += x1b * d * iG;
+                p1yb += y1b * d * iG;
+                double gbar = -(x1b * d * p1x + y1b * d * p1y) * (iG * iG);
                 double Fxb = 0.5 * d * p1xb, Fyb = 0.5 * d * p1yb;
                 double mxb = p1xb, myb = p1yb;
                 const double sb = -p1xb * qy + p1yb * qx;
@@ -215,19 +217,19 @@ __global__ __launch_bounds__(256) void k_push_adj(PushAdjArgs a) {
                 mxb += qxb + qyb * t;
                 myb += -qxb * t + qyb;
                 double tb = -qxb * my + qyb * mx;
-                tb += sb * 2.0 * (1.0 - t * t) / ((1.0 + t * t) * (1.0 + t * t));
-                const double bzb = tb * d / (2.0 * G_);
-                gbar += -tb * bz * d / (2.0 * G_ * G_);
+                tb += sb * 2.0 * (1.0 - t * t) * (it * it);
+                const double bzb = tb * d * (0.5 * iG);
+                gbar += -tb * bz * d * (0.5 * iG * iG);
                 double p0xb = mxb, p0yb = myb;
                 Fxb += 0.5 * d * mxb;
                 Fyb += 0.5 * d * myb;
-                const double gamb = Fxb * Gx / G_ + Fyb * Gy / G_;
-                const double Gxb = Fxb * gam / G_, Gyb = Fyb * gam / G_;
-                gbar += -(Fxb * gam * Gx + Fyb * gam * Gy) / (G_ * G_);
+                const double gamb = Fxb * Gx * iG + Fyb * Gy * iG;
+                const double Gxb = Fxb * gam * iG, Gyb = Fyb * gam * iG;
+                gbar += -(Fxb * gam * Gx + Fyb * gam * Gy) * (iG * iG);
                 const double byb = -Fxb, bxb = Fyb;
-                p0xb += gamb * p0x / G_;
-                p0yb += gamb * p0y / G_;
-                gbar += gamb * (G_ * G_ - 1.0 - p0x * p0x - p0y * p0y) / (2.0 * G_ * G_);
+                p0xb += gamb * p0x * iG;
+                p0yb += gamb * p0y * iG;
+                gbar += gamb * (G_ * G_ - 1.0 - p0x * p0x - p0y * p0y) * (0.5 * iG * iG);
                 xbar += Gxb * Gxi.dx + Gyb * Gyi.dx + bxb * bxi.dx + byb * byi.dx + bzb * bzi.dx;
                 ybar += Gxb * Gxi.dy + Gyb * Gyi.dy + bxb * bxi.dy + byb * byi.dy + bzb * bzi.dy;
                 if (own) {
@@ -248,9 +250,7 @@ __global__ __launch_bounds__(256) void k_push_adj(PushAdjArgs a) {
             }
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int m = 0; m < M; ++m) corner[c][r * M + m] = s[r][m];
+        for (int m = 0; m < M; ++m) join_corners<LANES>(s[0][m], s[1][m], s[2][m], s[3][m], l, corner[c] + m, M);
     }
     __syncthreads();
     double* out[M] = {a.Gxb, a.Gyb, a.Bxb, a.Byb, a.Bzb};
@@ -491,14 +491,17 @@ struct DepAdjArgs {
 
 // Deposits of j and T reversed (gathers of the node adjoints with the CIC
 // position derivatives; V = p / g), then the gather g = 1 + psi reversed.
-__global__ __launch_bounds__(256) void k_dep_adj(DepAdjArgs a) {
+template <int LANES>
+__global__ __launch_bounds__(kAdjThreads) void k_dep_adj(DepAdjArgs a) {
     __shared__ double corner[TC * TC][4];
     int tbx, tby;
     tile_of_block(tbx, tby);
     const int a0 = tbx * TN, b0 = tby * TN;
     const int N = a.N, pitch = a.pitch;
     const double h = a.h, L = a.L, wd = a.wd;
-    for (int c = threadIdx.x; c < TC * TC; c += blockDim.x) {
+    const double ih = 1.0 / h;
+    for (int i = threadIdx.x; i < LANES * TC * TC; i += kAdjThreads) {
+        const int c = i / LANES, l = i % LANES;
         const int cy = c / TC, cx = c - cy * TC;
         const int ga = a0 - 1 + cx, gb = b0 - 1 + cy;
         double s[4] = {0.0, 0.0, 0.0, 0.0};
@@ -522,15 +525,14 @@ __global__ __launch_bounds__(256) void k_dep_adj(DepAdjArgs a) {
             const double p00 = a.psi[g], p10 = a.psi[g + 1], p01 = a.psi[g + pitch],
                          p11 = a.psi[g + pitch + 1];
             const int k0 = a.start[cell], k1 = k0 + (a.start[cell + 1] - k0) * (valid ? 1 : 0);
-            for (int kb = k0; kb < k1; kb += kAdjBatch) {
-            const int cnt = min(kAdjBatch, k1 - kb);
+            for (int kb = k0 + l; kb < k1; kb += LANES * kAdjBatch) {
             // the batch's particles, the push's adjoint of g and the current
             // sums of the particle adjoints, all loads issued together
             double xv[kAdjBatch], yv[kAdjBatch], pxv[kAdjBatch], pyv[kAdjBatch], gv[kAdjBatch];
             double xo[kAdjBatch], yo[kAdjBatch], pxo[kAdjBatch], pyo[kAdjBatch];
 #pragma unroll
             for (int ib = 0; ib < kAdjBatch; ++ib) {
-                const int kk = kb + min(ib, cnt - 1);
+                const int kk = min(kb + LANES * ib, k1 - 1);
                 xv[ib] = a.x[kk];
                 yv[ib] = a.y[kk];
                 pxv[ib] = a.px[kk];
@@ -543,29 +545,29 @@ __global__ __launch_bounds__(256) void k_dep_adj(DepAdjArgs a) {
             }
 #pragma unroll
             for (int ib = 0; ib < kAdjBatch; ++ib) {
-                if (ib >= cnt) break;
-                const int k = kb + ib;
+                const int k = kb + LANES * ib;
+                if (k >= k1) break;
                 const double ddx = (xv[ib] + L) / h - ga, ddy = (yv[ib] + L) / h - gb;
-                const Interp gp = interp(p00, p10, p01, p11, ddx, ddy, h);
+                const Interp gp = interp(p00, p10, p01, p11, ddx, ddy, ih);
                 const double gi = 1.0 + gp.v;
-                const double vx = pxv[ib] / gi, vy = pyv[ib] / gi;
+                const double ig = 1.0 / gi, vx = pxv[ib] * ig, vy = pyv[ib] * ig;
                 const double q[5] = {vx, vy, vx * vx, vx * vy, vy * vy};
                 double qb[5], xbar = 0.0, ybar = 0.0;
 #pragma unroll
                 for (int m = 0; m < 5; ++m) {
-                    const Interp t = interp(A00[m], A10[m], A01[m], A11[m], ddx, ddy, h);
+                    const Interp t = interp(A00[m], A10[m], A01[m], A11[m], ddx, ddy, ih);
                     qb[m] = wd * t.v;
                     xbar += wd * q[m] * t.dx;
                     ybar += wd * q[m] * t.dy;
                 }
                 const double vxb = qb[0] + 2.0 * vx * qb[2] + vy * qb[3];
                 const double vyb = qb[1] + vx * qb[3] + 2.0 * vy * qb[4];
-                const double gtot = gv[ib] - (vxb * vx + vyb * vy) / gi;
+                const double gtot = gv[ib] - (vxb * vx + vyb * vy) * ig;
                 xbar += gtot * gp.dx;
                 ybar += gtot * gp.dy;
                 if (own) {
-                    a.pxb[k] = pxo[ib] + vxb / gi;
-                    a.pyb[k] = pyo[ib] + vyb / gi;
+                    a.pxb[k] = pxo[ib] + vxb * ig;
+                    a.pyb[k] = pyo[ib] + vyb * ig;
                     a.xb[k] = xo[ib] + xbar;
                     a.yb[k] = yo[ib] + ybar;
                 }
@@ -576,8 +578,7 @@ __global__ __launch_bounds__(256) void k_dep_adj(DepAdjArgs a) {
             }
             }
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) corner[c][r] = s[r];
+        join_corners<LANES>(s[0], s[1], s[2], s[3], l, corner[c], 1);
     }
     __syncthreads();
     double* out[1] = {a.psib_dep};
@@ -615,7 +616,7 @@ __global__ void k_n_adj_out(int64_t P, int N, double L, double h, double wd, int
         return nb[q] + (interior(N, qa, qb) ? lpsi[q] : 0.0);
     };
     const Interp t = interp(tot(g, a, b), tot(g + 1, a + 1, b), tot(g + pitch, a, b + 1),
-                            tot(g + pitch + 1, a + 1, b + 1), ddx, ddy, h);
+                            tot(g + pitch + 1, a + 1, b + 1), ddx, ddy, 1.0 / h);
     const int64_t k = id[j];
     adj_out[k] = xb[j] + wd * t.dx;
     adj_out[P + k] = yb[j] + wd * t.dy;
@@ -665,8 +666,8 @@ wandqs_status slice_adjoint(wandqs_ctx* c, const TapeSlot& ts, const double* d_f
         PushAdjArgs a{N, c->L, c->h, pitch, c->P, ts.pa[0], ts.pa[1], ts.pa[2], ts.pa[3], ts.pid,
                       ts.start, ts.fields[0], ts.fields[3], ts.fields[4], ts.fields[2], ts.st,
                       A.adj_id, A.xb, A.yb, A.pxb, A.pyb, A.gb, A.Gxb, A.Gyb, A.Bxb, A.Byb, A.Bzb};
-        ProfScope ps(c, "k_push_adj<16>", P * 108.0 + nnd * 76.0);
-        WQ_KLAUNCH(ps, k_push_adj, dim3(nt, nt), dim3(256), 0, s, a);
+        ProfScope ps(c, "k_push_adj", P * 108.0 + nnd * 76.0);
+        WQ_KLAUNCH(ps, k_push_adj<kAdjLanes>, dim3(nt, nt), dim3(kAdjThreads), 0, s, a);
     }
     {
         ProfScope ps(c, "k_grad_adj", nnd * 64.0);
@@ -729,8 +730,8 @@ wandqs_status slice_adjoint(wandqs_ctx* c, const TapeSlot& ts, const double* d_f
         DepAdjArgs d{N, c->L, c->h, wd, pitch, ts.pa[0], ts.pa[1], ts.pa[2], ts.pa[3], ts.start,
                      ts.fields[0], A.jxb, A.jyb, A.txxb, A.txyb, A.tyyb, A.gb, A.xb, A.yb, A.pxb,
                      A.pyb, A.psib_dep};
-        ProfScope ps(c, "k_dep_adj<16>", P * 104.0 + nnd * 60.0);
-        WQ_KLAUNCH(ps, k_dep_adj, dim3(nt, nt), dim3(256), 0, s, d);
+        ProfScope ps(c, "k_dep_adj", P * 104.0 + nnd * 60.0);
+        WQ_KLAUNCH(ps, k_dep_adj<kAdjLanes>, dim3(nt, nt), dim3(kAdjThreads), 0, s, d);
     }
     {
         ProfScope ps(c, "k_add_interior", nnd * 24.0);

@@ -25,7 +25,6 @@ constexpr int kNormVec = 6;     // per record and right-hand side r: sums of r^2
 // of eps (8/h^2 ||u|| + ||f||); one cycle before the floor, 0.5 or more.
 constexpr double kFloorBE = 0.35;
 constexpr int kTile = 32;       // multigrid tile edge (fine nodes owned by one workgroup)
-constexpr int kDepTile = 16;    // deposit tile edge (nodes owned by one workgroup)
 constexpr int kPredKinds = 8;   // solve kinds with their own V-cycle batch prediction
 constexpr int kThetaSeg = 4096; // nodes per partial sum of the driver-parameter adjoint
 #ifndef WQ_EXTRAP_ORDER
