@@ -34,9 +34,12 @@
 // A first form with two rows packed into one complex FFT of length 2n (the
 // odd extensions; 256 threads and a barrier per stage) measured 9.7 / 6.6 /
 // 5.3 us for the y / x inverse / x passes at n = 512, this one 7.5 / 5.4 /
-// 5.4.  TOP at n = 1024, averaged over one and two right-hand sides: x 23.6,
-// y 23.2, x inverse 13.2 us (1.6, 1.1 and 2.9 TB/s of its bytes; the transposed
-// 16-byte writes bound the first two); at n = 512 6.8 / 7.3 / 4.8.
+// 5.4.  TOP at n = 1024, averaged over one and two right-hand sides: x 16.1,
+// y 20.0, x inverse 11.7 us (2.3, 1.3 and 3.2 TB/s of its bytes; the transposed
+// writes and, in y, the registers bound the first two); at n = 512 6.3 / 7.1 /
+// 4.7.  With two LDS buffers per wavefront and the table's entries kept in scratch
+// they took 23.6 / 23.2 / 13.2 and 6.8 / 7.3 / 4.8; y at n = 1024 without the bound
+// of two wavefronts per SIMD (17 registers spilled) 21.4.
 #include <cstdio>
 
 #include "wq_common.h"
@@ -157,49 +160,52 @@ struct FstSize {
 // input t) times W_(NS R)^(k s), k = j mod NS, and puts its DFT at
 // (j - k) R + k + q NS.  The twiddles W_(NS R)^(k s) = W_n^(2 k s H / (NS R))
 // come from the LDS table T of W_n^m, m < H.
+// Every input is read before the first output is written, so that a stage may
+// work in place (half the LDS of two buffers, twice the wavefronts in flight).
 template <int H, int R, int NS, class Src>
 __device__ __forceinline__ void wstage(const Src& src, double* yr, double* yi, const double2* T) {
     constexpr int NBF = H / R, NBL = (NBF + 63) / 64;
+    double vr[NBL][R], vi[NBL][R];
 #pragma unroll
     for (int b = 0; b < NBL; ++b) {
-        const int j = (threadIdx.x & 63) + 64 * b;
-        if (NBF % 64 != 0 && j >= NBF) break;
+        const int j = min((int)(threadIdx.x & 63) + 64 * b, NBF - 1);
         const int k = j & (NS - 1);
-        double vr[R], vi[R];
 #pragma unroll
         for (int s = 0; s < R; ++s) {
             const double2 x = src(j + s * (H / R), b, s);
             if (NS > 1 && s > 0) {
                 const double2 w = twiddle<2 * H>(T, 2 * (k * s * (H / (NS * R))));
-                vr[s] = x.x * w.x - x.y * w.y;
-                vi[s] = x.x * w.y + x.y * w.x;
+                vr[b][s] = x.x * w.x - x.y * w.y;
+                vi[b][s] = x.x * w.y + x.y * w.x;
             } else {
-                vr[s] = x.x;
-                vi[s] = x.y;
+                vr[b][s] = x.x;
+                vi[b][s] = x.y;
             }
         }
-        dft<R>(vr, vi);
-        const int base = (j - k) * R + k;
+        dft<R>(vr[b], vi[b]);
+    }
+    wave_sync();
+#pragma unroll
+    for (int b = 0; b < NBL; ++b) {
+        const int j = (threadIdx.x & 63) + 64 * b;
+        if (NBF % 64 != 0 && j >= NBF) break;
+        const int k = j & (NS - 1), base = (j - k) * R + k;
 #pragma unroll
         for (int q = 0; q < R; ++q) {
-            yr[pidx(base + q * NS)] = vr[q];
-            yi[pidx(base + q * NS)] = vi[q];
+            yr[pidx(base + q * NS)] = vr[b][q];
+            yi[pidx(base + q * NS)] = vi[b][q];
         }
     }
 }
 
 template <int H, int NS, class Src>
-__device__ __forceinline__ void wfft(const Src& src, double* xr, double* xi, double* yr, double* yi,
-                                     const double2* T, double*& out_r, double*& out_i) {
+__device__ __forceinline__ void wfft(const Src& src, double* yr, double* yi, const double2* T) {
     constexpr int R = H / NS >= 4 ? 4 : H / NS;
     wstage<H, R, NS>(src, yr, yi, T);
     wave_sync();
     if constexpr (NS * R < H) {
         const auto lds = [yr, yi](int t, int, int) { return double2{yr[pidx(t)], yi[pidx(t)]}; };
-        wfft<H, NS * R>(lds, yr, yi, xr, xi, T, out_r, out_i);
-    } else {
-        out_r = yr;
-        out_i = yi;
+        wfft<H, NS * R>(lds, yr, yi, T);
     }
 }
 
@@ -207,12 +213,13 @@ __device__ __forceinline__ void wfft(const Src& src, double* xr, double* xi, dou
 // clamped indices only) by the lane: xe[q] = X_2k, xo[q] = X_2k+1 for
 // k = lane PER + q.  sn[b][s][e] = sin(pi j / n) of the lane's sample
 // j = 2m + e (m = the first-stage input of butterfly b, leg s), loaded by the
-// caller.  buf: 4 LP doubles of LDS (get may read it: its loads come first).
-// STORE: the lane's entries tv of the LDS table T (T[lane + 64 q] = tv[q]) are
+// caller.  buf: 2 LP doubles of LDS (get may read it: its loads come first).
+// STORE: the lane's entries tvr + i tvi of the LDS table T (T[lane + 64 q]) are
 // stored once the row's loads are issued, so that both sets of loads overlap.
 template <int LOGN, bool STORE, class Get>
 __device__ __forceinline__ void wdst(const Get& get, const double (&sn)[FstSize<LOGN>::NB][4][2],
-                                     double* buf, double2* T, const double2 (&tv)[FstSize<LOGN>::PER],
+                                     double* buf, double2* T, const double (&tvr)[FstSize<LOGN>::PER],
+                                     const double (&tvi)[FstSize<LOGN>::PER],
                                      double (&xe)[FstSize<LOGN>::PER], double (&xo)[FstSize<LOGN>::PER]) {
     using F = FstSize<LOGN>;
     constexpr int n = F::n, H = F::H, NB = F::NB, PER = F::PER, LP = F::LP;
@@ -234,7 +241,7 @@ __device__ __forceinline__ void wdst(const Get& get, const double (&sn)[FstSize<
         }
     if (STORE)
 #pragma unroll
-        for (int q = 0; q < PER; ++q) T[lane + 64 * q] = tv[q];
+        for (int q = 0; q < PER; ++q) T[lane + 64 * q] = double2{tvr[q], tvi[q]};
     wave_sync();
     double2 z[NB][4];
 #pragma unroll
@@ -247,12 +254,8 @@ __device__ __forceinline__ void wdst(const Get& get, const double (&sn)[FstSize<
                 y[e] = sn[b][s][e] * (xa[b][s][e] + xb[b][s][e]) + 0.5 * (xa[b][s][e] - xb[b][s][e]);
             z[b][s] = double2{y[0], y[1]};
         }
-    double* Ar = buf;
-    double* Ai = Ar + LP;
-    double* Br = Ai + LP;
-    double* Bi = Br + LP;
-    double *zr, *zi;
-    wfft<H, 1>([&](int, int b, int s) { return z[b][s]; }, Ar, Ai, Br, Bi, T, zr, zi);
+    double *zr = buf, *zi = buf + LP;
+    wfft<H, 1>([&](int, int b, int s) { return z[b][s]; }, zr, zi, T);
     // Y_k over the lane's chunk, then the prefix sum of Re Y (Re Y_0 halved)
     double rs[PER];
 #pragma unroll
@@ -295,10 +298,10 @@ __device__ __forceinline__ void wdst(const Get& get, const double (&sn)[FstSize<
 // incoming iterate, formed row by row in LDS, and records its norms; the
 // inverse x pass adds the correction to u.
 template <typename E, int LOGN, int MODE, int RW, bool TOP>
-__global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
+__global__ __launch_bounds__(64 * RW, (LOGN == 10 ? 2 : 1)) void k_fst(FstArgs<E> a) {
     using F = FstSize<LOGN>;
     constexpr int n = F::n, H = F::H, NB = F::NB, PER = F::PER, LP = F::LP;
-    __shared__ double bufs[RW][4 * LP];
+    __shared__ double bufs[RW][2 * LP];
     __shared__ double2 T[H];
     int pb, r;
     tile_of_block(pb, r);
@@ -308,9 +311,12 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
     double* buf = bufs[w];
     // tables: W_n^m (m < H) = W_2n^2m into LDS; the lane's sin(pi j / n) =
     // -Im W_2n^j; for MODE 1 its sin^2(pi l / 2n) and that of k = p + 1
-    double2 tv[PER];
+    double tvr[PER], tvi[PER];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) tv[q] = a.tw[2 * (lane + 64 * q)];
+    for (int q = 0; q < PER; ++q) {
+        tvr[q] = a.tw[2 * (lane + 64 * q)].x;
+        tvi[q] = a.tw[2 * (lane + 64 * q)].y;
+    }
     double sn[NB][4][2];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -322,7 +328,7 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
                 sn[b][s][e] = -a.tw[2 * m + e].y;
             }
     double s2e[MODE == 1 ? PER : 1], s2o[MODE == 1 ? PER : 1], s2k = 0.0;
-    if (MODE == 1) {
+    if constexpr (MODE == 1) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int k = lane * PER + q;
@@ -344,19 +350,21 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
             for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], d, 64);
         if (lane < 3 && live)
             a.norm_part[(size_t)(3 * r + lane) * a.nblk + p] = lane == 0 ? s[0] : lane == 1 ? s[1] : s[2];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) T[lane + 64 * q] = double2{tvr[q], tvi[q]};
         wave_sync();
         const auto get = [=](int j) { return V[pidx(j)]; };
-        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+        wdst<LOGN, false>(get, sn, buf, T, tvr, tvi, xe, xo);
     } else if (MODE == 0) {
         const E* row = a.f[r] + (size_t)(p + 1) * a.pitch;
         const auto get = [=](int j) { return (double)row[j]; };
-        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+        wdst<LOGN, true>(get, sn, buf, T, tvr, tvi, xe, xo);
     } else {
         const double* row = (MODE == 1 ? a.t1 : a.t2)[r] + (size_t)p * ld - 1;
         const auto get = [=](int j) { return row[j]; };
-        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+        wdst<LOGN, true>(get, sn, buf, T, tvr, tvi, xe, xo);
     }
-    if (MODE == 1) {
+    if constexpr (MODE == 1) {
         // coefficient (k, l) over its eigenvalue, into LDS by l (V[0] = 0),
         // then transformed back along y
         double* V = buf;
@@ -369,7 +377,7 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
         }
         wave_sync();
         const auto get = [=](int j) { return V[pidx(j)]; };
-        wdst<LOGN, false>(get, sn, buf, T, tv, xe, xo);
+        wdst<LOGN, false>(get, sn, buf, T, tvr, tvi, xe, xo);
     }
     if (MODE < 2 && RW == 1) {
         // coefficient c (1 .. n-1) of this row to T[c - 1][p]
@@ -436,8 +444,9 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
 }
 
 // Rows per workgroup of the x and y passes, whose transposed writes then go
-// out in 16-byte pieces: at n = 512 they measured 5.4 / 7.5 us with 2 rows,
-// 6.1 / 8.0 with 1 and 5.7 / 8.0 with 4 (the same bits in every case)
+// out in 16-byte pieces: TOP at n = 512 measured 6.3 / 7.1 us with 2 rows, 6.9 /
+// 7.6 with 1 and 8.2 / 7.8 with 4; at n = 1024, where the writes count more, 4
+// rows 16.1 / 21.4, 2 rows 18.0 / 24.2 (the same bits in every case)
 #ifndef WQ_FST_ROWS
 #define WQ_FST_ROWS 2
 #endif
@@ -445,7 +454,7 @@ __global__ __launch_bounds__(64 * RW) void k_fst(FstArgs<E> a) {
 template <typename E, int LOGN, bool TOP>
 void launch_fst(wandqs_ctx* c, const FstArgs<E>& a, int R, const char* tname) {
     constexpr int n = 1 << LOGN;
-    constexpr int RW = LOGN <= 10 ? WQ_FST_ROWS : 1;
+    constexpr int RW = LOGN == 10 ? 2 * WQ_FST_ROWS : LOGN < 10 ? WQ_FST_ROWS : 1;
     const dim3 g(n - 1, R), gw((n - 1 + RW - 1) / RW, R);
     const double nodes = (double)(n - 1) * (n - 1) * R;
     const double eb = sizeof(E);
@@ -476,7 +485,7 @@ void launch_fst(wandqs_ctx* c, const FstArgs<E>& a, int R, const char* tname) {
 // wavefront each: T1 and T2 hold (re, im) pairs, so that the transposed writes
 // of the x and y passes go out in 32-byte pieces (two rows per workgroup), and
 // the y pass exchanges the parts' coefficients through LDS for the complex
-// division.  At 512^2 x 9.1, y 11.1, x inverse 6.9 us (1.8, 0.75 and 1.8 TB/s of
+// division.  At 512^2 x 7.1, y 9.8, x inverse 5.8 us (2.4, 0.85 and 2.2 TB/s of
 // its bytes; the two transforms of the y pass and its scattered writes bound
 // that one).  A plane of a pulse with the plasma behind its front (512^2) takes
 // 6 of these instead of 9.4 V-cycles of 95 us: its time step of 20 planes 31.2
@@ -502,7 +511,7 @@ __global__ __launch_bounds__((128 * las_rows<LOGN, MODE>())) void k_las_fst(LasF
     using F = FstSize<LOGN>;
     constexpr int n = F::n, H = F::H, NB = F::NB, PER = F::PER, LP = F::LP;
     constexpr int RW = las_rows<LOGN, MODE>();
-    __shared__ double bufs[2 * RW][4 * LP];
+    __shared__ double bufs[2 * RW][2 * LP];
     __shared__ double2 T[H];
     int pb, r0;
     tile_of_block(pb, r0);
@@ -511,9 +520,12 @@ __global__ __launch_bounds__((128 * las_rows<LOGN, MODE>())) void k_las_fst(LasF
     const int p = live ? pb * RW + (w >> 1) : n - 2;
     double* buf = bufs[w];
     double *V0 = bufs[w & ~1], *V1 = bufs[w | 1];  // the row's real and imaginary part
-    double2 tv[PER];
+    double tvr[PER], tvi[PER];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) tv[q] = a.tw[2 * (lane + 64 * q)];
+    for (int q = 0; q < PER; ++q) {
+        tvr[q] = a.tw[2 * (lane + 64 * q)].x;
+        tvi[q] = a.tw[2 * (lane + 64 * q)].y;
+    }
     double sn[NB][4][2];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -557,11 +569,11 @@ __global__ __launch_bounds__((128 * las_rows<LOGN, MODE>())) void k_las_fst(LasF
         }
         __syncthreads();
         const auto get = [=](int j) { return buf[pidx(j)]; };
-        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+        wdst<LOGN, true>(get, sn, buf, T, tvr, tvi, xe, xo);
     } else {
         const double* row = (MODE == 1 ? a.t1 : a.t2) + 2 * ((size_t)p * ld - 1) + part;
         const auto get = [=](int j) { return row[2 * j]; };
-        wdst<LOGN, true>(get, sn, buf, T, tv, xe, xo);
+        wdst<LOGN, true>(get, sn, buf, T, tvr, tvi, xe, xo);
     }
     if constexpr (MODE == 1) {
         // coefficient (k, l) over its eigenvalue er + i gam, then back along y
@@ -591,7 +603,7 @@ __global__ __launch_bounds__((128 * las_rows<LOGN, MODE>())) void k_las_fst(LasF
         }
         wave_sync();
         const auto get = [=](int j) { return buf[pidx(j)]; };
-        wdst<LOGN, false>(get, sn, buf, T, tv, xe, xo);
+        wdst<LOGN, false>(get, sn, buf, T, tvr, tvi, xe, xo);
     }
 #pragma unroll
     for (int q = 0; q < PER; ++q) {

@@ -580,7 +580,7 @@ namespace {
 // with kbar = kr - i gam, kr the middle of Re k's range on the interior nodes, an
 // iteration multiplies the residual's 2-norm by rho = (half the range) /
 // |kr - i gam| at most, as -L_h > 0.  A V-cycle gains a factor 20 to 25 and takes
-// 95 us at 512^2, an iteration 27 us, so the iterations are taken up to rho = 0.4, where they gain
+// 95 us at 512^2, an iteration 23 us, so the iterations are taken up to rho = 0.4, where they gain
 // as much per time, if mg_max_cycles leaves room for the count that rho ensures
 // (to 1e-16).  An unbounded or undefined k goes to the V-cycles.
 constexpr double kLasDirectRho = 0.4;
