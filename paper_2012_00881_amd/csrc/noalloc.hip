@@ -81,9 +81,7 @@ extern "C" wandqs_status wandqs_mg_solve_noalloc(const wandqs_config* cfg, int32
     wq::Level& L0 = c.lev[0];
     if ((s = wq::fill_f64(&c, reinterpret_cast<double*>(base), need / sizeof(double), 0.0)) != WANDQS_OK ||
         (s = wq::make_dst_tables(&c)) != WANDQS_OK ||
-        (s = wq::unpack_fields(&c, d_f, nrhs, L0.f)) != WANDQS_OK ||
-        (s = wq::unpack_fields(&c, d_u, nrhs, c.fields)) != WANDQS_OK ||
-        (d_k2 && (s = wq::unpack_fields(&c, d_k2, 1, &L0.k2)) != WANDQS_OK)) {
+        (s = wq::unpack_solve(&c, nrhs, d_f, d_u, d_k2)) != WANDQS_OK) {
         wq::set_call_error(c.err.c_str());
         return s;
     }

@@ -108,37 +108,29 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const int32_t* __r
     if (threadIdx.x == kScanThreads - 1) blk[blockIdx.x] = tot[kScanThreads - 1];
 }
 
-// Phase 2: one block scans the block totals (serial chunks per thread) and
-// writes the grand total to out[n].
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(int32_t* __restrict__ blk, int nb,
-                                                           int32_t* __restrict__ out, int n) {
-    __shared__ int32_t tot[kScanThreads];
-    const int per = (nb + kScanThreads - 1) / kScanThreads;
-    const int b0 = threadIdx.x * per;
+// Phase 2: block b adds the totals of the blocks before it (which it sums for
+// itself: a launch that scans the totals first cost 4 us a slice, reading them
+// nb times over is 4 MB at 1024^2) to its kScanBlock items; the last one writes
+// the grand total to out[n].
+__global__ __launch_bounds__(kScanThreads) void k_scan_add(int32_t* __restrict__ out, int n,
+                                                           const int32_t* __restrict__ blk) {
+    __shared__ int32_t part[kScanThreads / 64];
+    const int b = blockIdx.x, base = b * kScanBlock + threadIdx.x * kScanItems;
+    int32_t v[kScanItems];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) v[k] = out[min(base + k, n - 1)];
     int32_t s = 0;
-    for (int k = 0; k < per; ++k)
-        if (b0 + k < nb) s += blk[b0 + k];
-    tot[threadIdx.x] = s;
+    for (int k = threadIdx.x; k < b; k += kScanThreads) s += blk[k];
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int off = 1; off < kScanThreads; off <<= 1) {
-        int32_t t = threadIdx.x >= off ? tot[threadIdx.x - off] : 0;
-        __syncthreads();
-        tot[threadIdx.x] += t;
-        __syncthreads();
-    }
-    int32_t run = tot[threadIdx.x] - s;
-    for (int k = 0; k < per; ++k)
-        if (b0 + k < nb) {
-            const int32_t t = blk[b0 + k];
-            blk[b0 + k] = run;
-            run += t;
-        }
-    if (threadIdx.x == kScanThreads - 1) out[n] = tot[kScanThreads - 1];
-}
-
-__global__ void k_scan_add(int32_t* __restrict__ out, int n, const int32_t* __restrict__ blk) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] += blk[i / kScanBlock];
+    s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanThreads / 64; ++k) s += part[k];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k)
+        if (base + k < n) out[base + k] = v[k] + s;
+    if (b == (int)gridDim.x - 1 && threadIdx.x == 0) out[n] = s + blk[b];
 }
 
 // Scatter: count[] is consumed back to zero, ready for the next slice.  One
@@ -740,14 +732,8 @@ wandqs_status slice_sort(wandqs_ctx* c) {
                            c->cell_start, c->scan_blk);
     }
     {
-        ProfScope ps(c, "k_scan_top", 8.0 * nb);
-        WQ_KLAUNCH(ps, k_scan_top, dim3(1), dim3(kScanThreads), 0, s, c->scan_blk, nb,
-                           c->cell_start, ncell);
-    }
-    {
         ProfScope ps(c, "k_scan_add", (double)ncell * 8.0);
-        WQ_KLAUNCH(ps, k_scan_add, dim3(blocks_for(ncell, 256)), dim3(256), 0, s, c->cell_start,
-                           ncell, c->scan_blk);
+        WQ_KLAUNCH(ps, k_scan_add, dim3(nb), dim3(kScanThreads), 0, s, c->cell_start, ncell, c->scan_blk);
     }
     {
         ProfScope ps(c, "k_scatter", (double)c->P * 12.0 + (double)ncell * 8.0);

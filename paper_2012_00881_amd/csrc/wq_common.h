@@ -427,6 +427,8 @@ wandqs_status push_and_step(wandqs_ctx* c, int rec_slot, bool grad_ready = false
 wandqs_status probes_accumulate(wandqs_ctx* c, int64_t slice);
 wandqs_status pack_fields(wandqs_ctx* c, double* const* src, int n, double* dst);
 wandqs_status unpack_fields(wandqs_ctx* c, const double* src, int n, double* const* dst);
+// the inputs of a solve: f and u (nrhs each) into lev[0].f and fields, k2 (or null) into lev[0].k2
+wandqs_status unpack_solve(wandqs_ctx* c, int nrhs, const double* f, const double* u, const double* k2);
 wandqs_status particles_to_id_order(wandqs_ctx* c, double* dst);
 wandqs_status particles_from_id_order(wandqs_ctx* c, const double* src);
 wandqs_status fill_f64(wandqs_ctx* c, double* p, size_t n, double v);
