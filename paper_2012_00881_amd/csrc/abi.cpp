@@ -378,8 +378,8 @@ void carve_dst(wandqs_ctx* c, Take&& take, bool top) {
         const size_t n = c->lev[top ? 0 : 1].N, one = (n - 1) * (n + 8);
         c->fst_t1[0] = (double*)take(sizeof(double) * 2 * one);
         c->fst_t2[0] = (double*)take(sizeof(double) * 2 * one);
-        c->fst_t1[1] = c->fst_t1[0] + one;
-        c->fst_t2[1] = c->fst_t2[0] + one;
+        c->fst_t1[1] = c->fst_t1[0] ? c->fst_t1[0] + one : nullptr;  // (null: sizing pass)
+        c->fst_t2[1] = c->fst_t2[0] ? c->fst_t2[0] + one : nullptr;
     }
     if (top) {
         c->fst_top_tw = (double2*)take(sizeof(double2) * 2 * (size_t)c->N);
