@@ -240,10 +240,43 @@ struct FieldPtrs {
     double* out[5];
 };
 
-// Every workgroup forms the Lagrange weights w[m] of p_m relative to u for itself
-// (thread m; a launch for them alone cost 4 us a slice): the order drops while two
+// The first LINEAR fields extrapolate through the last two slices only (weight
+// w[0] of p1): the exact solve of psi, E_z and B_z reaches the rounding floor in
+// one iteration from there as well, and their older history need not be read (at
+// 1024^2 35.4 -> 26.9 us; from u itself some slices took two).  Every load of a node is
+// issued before the first is used.
+template <int ORDER, int LINEAR>
+__device__ __forceinline__ void extrapolate_node(const FieldPtrs& f, size_t g, const double* w) {
+    double u[5], p[5][3];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        u[k] = f.u[k][g];
+        if (ORDER >= 1) p[k][0] = f.p1[k][g];
+        if (k >= LINEAR) {
+            if (ORDER >= 2) p[k][1] = f.p2[k][g];
+            if (ORDER >= 3) p[k][2] = f.p3[k][g];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        double v = u[k];
+        if (k < LINEAR) {
+            if (ORDER >= 1) v = u[k] + w[0] * (p[k][0] - u[k]);
+        } else {
+            if (ORDER == 1) v = u[k] + w[1] * (p[k][0] - u[k]);
+            if (ORDER == 2) v = u[k] + (w[1] * (p[k][0] - u[k]) + w[2] * (p[k][1] - u[k]));
+            if (ORDER == 3)
+                v = u[k] + (w[1] * (p[k][0] - u[k]) + w[2] * (p[k][1] - u[k]) + w[3] * (p[k][2] - u[k]));
+        }
+        f.out[k][g] = v;
+    }
+}
+
+// Every workgroup forms the Lagrange weights w[m] of p_m relative to u (w[0]: of p1
+// in the linear form) for itself (thread m; a launch for them alone cost 4 us a slice): the order drops while two
 // of the points coincide.
 constexpr int kExtraThreads = 128;
+template <int LINEAR>
 __global__ __launch_bounds__(kExtraThreads) void k_extrapolate(int N, int pitch, const double* __restrict__ st,
                                                                int order, FieldPtrs f) {
     __shared__ double w[4];
@@ -258,29 +291,22 @@ __global__ __launch_bounds__(kExtraThreads) void k_extrapolate(int N, int pitch,
         return ok;
     };
     while (order > 0 && !differ(order)) --order;
-    if (threadIdx.x >= 1 && threadIdx.x < 4) {
-        const int i = threadIdx.x;
+    if (threadIdx.x < 4) {
+        const int i = max((int)threadIdx.x, 1), deg = threadIdx.x == 0 ? 1 : order;
         const double xi = st[0], xm = st[2 + i];
         double l = 1.0;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (j <= order && j != i) l *= (xi - x[j]) / (xm - x[j]);
-        w[i] = l;
+            if (j <= deg && j != i) l *= (xi - x[j]) / (xm - x[j]);
+        w[threadIdx.x] = l;
     }
     __syncthreads();
     if (a > N) return;
-    const double w1 = w[1], w2 = w[2], w3 = w[3];
     const size_t g = (size_t)blockIdx.y * pitch + a;
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const double u = f.u[k][g];
-        double v = u;
-        if (order == 1) v = u + w1 * (f.p1[k][g] - u);
-        if (order == 2) v = u + (w1 * (f.p1[k][g] - u) + w2 * (f.p2[k][g] - u));
-        if (order == 3)
-            v = u + (w1 * (f.p1[k][g] - u) + w2 * (f.p2[k][g] - u) + w3 * (f.p3[k][g] - u));
-        f.out[k][g] = v;
-    }
+    if (order >= 3) extrapolate_node<3, LINEAR>(f, g, w);
+    else if (order == 2) extrapolate_node<2, LINEAR>(f, g, w);
+    else if (order == 1) extrapolate_node<1, LINEAR>(f, g, w);
+    else extrapolate_node<0, LINEAR>(f, g, w);
 }
 
 __global__ void k_fill(double* p, size_t n, double v) {
@@ -441,9 +467,14 @@ wandqs_status extrapolate_guess(wandqs_ctx* c, int order) {
     }
     order = order < 0 ? 0 : (order > kGuessMax - 1 ? kGuessMax - 1 : order);
     {
-        ProfScope ps(c, "k_extrapolate", (double)(c->N + 1) * (c->N + 1) * 5 * 8.0 * (order + 2));
-        WQ_KLAUNCH(ps, k_extrapolate, node_grid(c->N), dim3(kExtraThreads), 0, c->stream, c->N,
-                   c->lev[0].pitch, c->st, order, f);
+        const bool lin = direct_poisson(c, false);
+        ProfScope ps(c, "k_extrapolate", (double)(c->N + 1) * (c->N + 1) * 8.0 * (lin ? 3 * (std::min(order, 1) + 2) + 2 * (order + 2) : 5 * (order + 2)));
+        if (lin)
+            WQ_KLAUNCH(ps, k_extrapolate<3>, node_grid(c->N), dim3(kExtraThreads), 0, c->stream, c->N,
+                       c->lev[0].pitch, c->st, order, f);
+        else
+            WQ_KLAUNCH(ps, k_extrapolate<0>, node_grid(c->N), dim3(kExtraThreads), 0, c->stream, c->N,
+                       c->lev[0].pitch, c->st, order, f);
     }
     WQ_LAUNCH_CHECK();
     for (int k = 0; k < 5; ++k) {  // oldest <- ... <- prev <- u <- guess

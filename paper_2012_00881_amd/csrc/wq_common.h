@@ -395,6 +395,8 @@ void fst_solve(wandqs_ctx* c, int R, const E* const* f, E* const* u);
 bool fst_top_used(const wandqs_ctx* c);
 void fst_top_iteration(wandqs_ctx* c, int R, const double* const* f, double* const* u,
                        double* norm_part);
+// Whether a solve of this context iterates with the exact sine-transform solve (mg.hip)
+bool direct_poisson(const wandqs_ctx* c, bool helm);
 // One iteration u += (L_h - kr + i gam)^-1 (f - (L_h - k) u) of a laser envelope
 // plane by sine transforms (grids with fst_top_tw).
 void las_fst_iteration(wandqs_ctx* c, const double2* f, const double2* k, double2* u, double kr, double gam);
