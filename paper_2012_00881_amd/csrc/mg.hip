@@ -2743,7 +2743,7 @@ bool direct_poisson(const wandqs_ctx* c, bool helm) {
 
 // Solve with the context's stop rule.  Tolerance mode (mg_rtol > 0) runs a batch
 // of V-cycles sized by the previous slice's count for this solve, reads the
-// residual norms back once per batch and adds single cycles until every
+// residual norms back once per batch and adds batches sized by its gain until every
 // right-hand side meets ||r|| <= rtol ||f|| + atol sqrt(n) or reaches the
 // rounding floor: either ||r|| <= kFloorBE eps (8/h^2 ||u|| + ||f||) (the
 // residual is at the size that rounding in forming it leaves), or a cycle no
@@ -2867,14 +2867,14 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
     const dim3 fg = fuse_grid(c, R);
     const int nblk_fuse = fg.x * fg.y;
     int cur = 0;
-    int done = 0;
+    int done = 0, more = 1;
     int pred = c->pred[kind] < 1 ? 1 : c->pred[kind];
     double* hr = c->h_pin;  // [kMaxSlots][kNormVec] + flags
     constexpr int V = kNormVec;
     const double a_norm = 8.0 / (c->lev[0].h * c->lev[0].h);  // ||L_h||_2 bound
     const double eps = std::numeric_limits<double>::epsilon();
     while (true) {
-        int b = done == 0 ? pred : 1;
+        int b = done == 0 ? pred : more;
         if (done + b > maxc) b = maxc - done;
         if (whole && direct) whole_direct(c, R, hz, b, done);
         else if (whole) whole_cycles(c, R, helm, hz, b, inner, done);
@@ -2961,6 +2961,19 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
             // iterate only when enqueued again
             if (!first && ahead) return ahead();
             return WANDQS_OK;
+        }
+        // the next batch: the cycles that the last one's gain leaves to do for the
+        // right-hand side that is furthest off, rounded down (single cycles cost
+        // a norm check each: the slice behind a restored state, whose own solve
+        // predicts none, took eight batches at 64^2)
+        more = 1;
+        for (int r = 0; r < R; ++r) {
+            const double rr = std::sqrt(hr[V * done + 3 * r]), rp = std::sqrt(hr[V * (done - 1) + 3 * r]);
+            const double ff = std::sqrt(hr[V * done + 3 * r + 1]), uu = std::sqrt(hr[V * done + 3 * r + 2]);
+            const double goal = std::max(c->cfg.mg_rtol * (ff > 0 ? ff : std::sqrt(hr[3 * r])) + atol,
+                                         kFloorBE * eps * (a_norm * uu + ff));
+            const double left = std::log(goal / rr) / std::log(rr / rp);
+            if (rr > goal && left > more && left < maxc) more = (int)left;
         }
     }
 }
