@@ -2963,9 +2963,10 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
             return WANDQS_OK;
         }
         // the next batch: the cycles that the last one's gain leaves to do for the
-        // right-hand side that is furthest off, rounded down (single cycles cost
-        // a norm check each: the slice behind a restored state, whose own solve
-        // predicts none, took eight batches at 64^2)
+        // right-hand side that is furthest off, rounded down and one fewer (later
+        // cycles gain more than the first).  Single cycles cost a norm check each:
+        // the slice behind a restored state, whose own solve predicts none, took
+        // eight batches at 64^2, now four or five.
         more = 1;
         for (int r = 0; r < R; ++r) {
             const double rr = std::sqrt(hr[V * done + 3 * r]), rp = std::sqrt(hr[V * (done - 1) + 3 * r]);
@@ -2973,7 +2974,7 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
             const double goal = std::max(c->cfg.mg_rtol * (ff > 0 ? ff : std::sqrt(hr[3 * r])) + atol,
                                          kFloorBE * eps * (a_norm * uu + ff));
             const double left = std::log(goal / rr) / std::log(rr / rp);
-            if (rr > goal && left > more && left < maxc) more = (int)left;
+            if (rr > goal && left >= more + 2.0 && left < maxc) more = (int)left - 1;
         }
     }
 }
