@@ -1273,15 +1273,6 @@ __device__ __forceinline__ void coarse_prolong(C (&uR)[NP], C (&uB)[NP], const C
     }
 }
 
-// The Helmholtz V-cycles of larger grids end on the level of 8 cells with
-// over-relaxed sweeps in place of two more levels: with omega >= 2 / (1 + sin(pi
-// / 8)) = 1.446, the optimum for k2 = 0, a sweep contracts by omega - 1 at least,
-// four by 0.04, less than a V-cycle leaves.  One coarse launch (two cycles) 14.3
-// instead of 15.7 us with the same number of V-cycles.  Poisson V-cycles keep the
-// exact 2-cell level: with four sweeps instead they took twice as many.
-constexpr int kBottomN = 8, kBottomSweeps = 4;
-constexpr double kBottomOmega = 1.45;
-
 // A level of n <= 32 cells in the calling wavefront.
 template <typename C, int n, bool HELM>
 struct CoarseWave {
@@ -1340,17 +1331,6 @@ struct CoarseWave {
     __device__ __forceinline__ void cycle(C (&uR)[NP], C (&uB)[NP], const C (&fR)[NP], const C (&fB)[NP],
                                           int nu1, int nu2, double omega, double h2max, double k2_two) const {
         constexpr int nc = n / 2;
-        if constexpr (HELM && n == kBottomN) {
-            C iR[NP], iB[NP];
-            table(lds.id, 0, iR);
-            table(lds.id, 1, iB);
-#pragma unroll
-            for (int s = 0; s < kBottomSweeps; ++s) {
-                coarse_half<C, NP>(uR, fR, iR, uB, edge(uB, p), p, h2, C(kBottomOmega));
-                coarse_half<C, NP>(uB, fB, iB, uR, edge(uR, !p), !p, h2, C(kBottomOmega));
-            }
-            return;
-        }
         smooth(uR, uB, fR, fB, nu1);
         C rR[NP], rB[NP];
         {
@@ -1368,7 +1348,11 @@ struct CoarseWave {
         const C below = __shfl(t[NP - 1], (lane - n) & 63, 64);  // (row -1: only of coarse row 0)
         coarse_restrict<C, NP>(v, rR, rB, below, p);
         if constexpr (n == 4) {
-            // 2 x 2 cells: one unknown, four zero neighbours, solved in double
+            // 2 x 2 cells: one unknown, four zero neighbours, solved in double.  (The
+            // cycle has to end exactly: four over-relaxed sweeps on the 8-cell level
+            // in place of the levels below it take 1.2 us less a launch, but
+            // where k2 is close to 0 they leave 0.7 of the worst error and a cycle
+            // then gains 8 instead of 30.)
             const double f2 = (double)__shfl(v[0], 4 + 2, 64), H = 2.0 * h;
             if (lane == 0) lds.E[coarse_off_E(2) + 4] = (C)(-f2 / (4.0 / (H * H) + k2_two));
             wave_sync();
