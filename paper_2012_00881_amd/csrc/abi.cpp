@@ -1077,7 +1077,7 @@ wandqs_status wandqs_mg_solve(wandqs_ctx* c, int32_t nrhs, const double* d_k2, c
     double* f[2] = {L0.f[0], nrhs > 1 ? L0.f[1] : nullptr};
     c->n_guess = 0;  // the stored fields no longer belong to the slice sequence
     c->tape_ok = false;
-    s = wq::mg_solve(c, 3, nrhs, d_k2 != nullptr, u, f, d_k2 ? L0.k2 : nullptr, &res);
+    s = wq::mg_solve(c, d_k2 ? wq::kSolveUserHelm : wq::kSolveUser, nrhs, d_k2 != nullptr, u, f, d_k2 ? L0.k2 : nullptr, &res);
     if (s != WANDQS_OK && s != WANDQS_E_NOCONV) return fail(c, s);
     wandqs_status s2 = wq::pack_fields(c, c->fields, nrhs, d_u);
     if (s2 != WANDQS_OK) return fail(c, s2);

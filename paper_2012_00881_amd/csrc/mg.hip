@@ -2934,7 +2934,7 @@ wandqs_status mg_solve(wandqs_ctx* c, int kind, int R, bool helm, double* const 
             if (need < 0) {
                 static const char* names[kPredKinds] = {"psi", "Ez/Bz", "B_perp", "user",
                                                         "psi adjoint", "Ez/Bz adjoint",
-                                                        "B_perp adjoint", "?"};
+                                                        "B_perp adjoint", "user"};
                 c->err = std::string("multigrid did not converge within mg_max_cycles (") +
                          names[kind & (kPredKinds - 1)] + " solve, ||r||/||f|| = " +
                          std::to_string(res ? res->rel[0] : -1.0) + ")";

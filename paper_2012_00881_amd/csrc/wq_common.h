@@ -110,10 +110,11 @@ enum SolveKind {
     kSolvePsi = 0,
     kSolveEB = 1,
     kSolveBperp = 2,
-    kSolveUser = 3,
+    kSolveUser = 3,  // Poisson
     kSolvePsiAdj = 4,
     kSolveEBAdj = 5,
-    kSolveBperpAdj = 6
+    kSolveBperpAdj = 6,
+    kSolveUserHelm = 7
 };
 
 // Checkpoint of the slice loop state (the adjoint recomputes from it).
