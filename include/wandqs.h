@@ -117,8 +117,9 @@ typedef struct {
     int32_t nu_pre, nu_post; /* over-relaxed red-black Gauss-Seidel sweeps per V-cycle,
                                 each 1 .. 3; the levels two or more below the
                                 finest pre-smooth with one sweep, and in the
-                                tolerance mode the Helmholtz levels of at most
-                                64^2 below a finer one run two V(1, 1) cycles */
+                                tolerance mode with nu_post >= 2 the Helmholtz
+                                levels of at most 64^2 below a finer one run two
+                                cycles of one sweep fewer each way (at least one) */
     int32_t n_beams;       /* 0 .. 8 */
     const wandqs_beam* beams;
     int32_t n_probes;      /* 0 .. 16 */

@@ -50,13 +50,14 @@ constexpr double kOmegaH2N0 = 0.125;
 // (measured).  The finer levels and every post-smoothing keep nu_pre, nu_post.
 constexpr int kFullPreLevels = 2;
 // In the tolerance mode the Helmholtz V-cycles visit the levels of at most 64^2
-// with two V(1, 1) cycles instead of one V(1, nu_post): a further cycle there
+// with two cycles of a sweep fewer each way (at least one), two V(1, 1) instead of
+// one V(1, 2) by default; nu_post = 1 keeps its one cycle.  A further cycle there
 // costs about 4 us inside the launch and takes B_perp from 8.8 to 6.1 V-cycles per
 // solve at 256^2, from 7.6 to 6.2 at 512^2 and from 6.2 to 5.4 at 1024^2 (slices of
 // 477 -> 402, 763 -> 722 and 1065 -> 1032 us; V(1, 2) twice 415, 740, 1043; three
 // V(1, 1) with two pre-sweeps on every tile level 432, 723, 1056).  Fixed mode
 // keeps the single cycle its callers count.
-constexpr int kCoarseCycles = 2, kCoarseNu = 1;
+constexpr int kCoarseCycles = 2;
 // Tile kernels: 32 x 32 owned nodes with 512 threads, or 16 x 16 with 256
 // threads on the levels N <= WQ_SMALL_TILE_MAX (more workgroups and a shorter
 // chain of dependent LDS phases per workgroup where the grid is small).
@@ -2512,9 +2513,10 @@ void vcycle(wandqs_ctx* c, int R, bool helm, const Hier<E>& hz, bool zero_guess,
             a.ncycles = 1;
             a.inner = 1;
             a.nu1 = nu_pre_at(c, lc);
-            if (c->cfg.mg_rtol > 0.0) {
+            if (c->cfg.mg_rtol > 0.0 && a.nu2 >= 2) {
                 a.inner = kCoarseCycles;
-                a.nu1 = a.nu2 = kCoarseNu;
+                a.nu1 = std::max(1, a.nu1 - 1);
+                --a.nu2;
             }
             prof_name(c, nm, sizeof nm, "k_mg_coarse<%s, %s, true, 64>", type_name(E()), type_name(CT()));
             ProfScope ps(c, nm, nodes * (2.0 * eb * R + 2.0 * sizeof(CT)));
