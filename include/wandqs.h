@@ -336,7 +336,8 @@ wandqs_status wandqs_mg_solve(wandqs_ctx* ctx, int32_t nrhs, const double* d_k2,
  *   R J = J + (1/3)(hb_x dx + hb_y dy) J,
  * nine-point and not symmetric; on a uniform grid the 5-point Laplacian + M.
  * V-cycles with alternating zebra line relaxation on every level (one step
- * before and one after the coarse correction), coarse grids with every other
+ * before and one after the coarse correction; on the levels of at most 64^2
+ * (nu_pre + 1) / 2 and (nu_post + 1) / 2 steps), coarse grids with every other
  * node, linear interpolation in the coordinates as prolongation
  * and its control-volume weighted transpose as restriction (for M too);
  * the context's stop rule (mg_rtol, mg_atol, the rounding floor with

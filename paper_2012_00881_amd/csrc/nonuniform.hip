@@ -14,10 +14,11 @@
 // uniform grid).
 //
 // The solver: V-cycles smoothing by alternating zebra line relaxation (x-lines
-// of odd then even rows, y-lines of odd then even columns, once before and once
-// after the coarse correction: cells of aspect ratio up to 3 defeat point
-// smoothers); coarse grids keep every other node and rediscretise L; the
-// prolongation interpolates linearly in the coordinates and the restriction
+// of odd then even rows, y-lines of odd then even columns, one such step before and
+// one after the coarse correction, on the levels of N <= 64 (nu + 1) / 2 of them for
+// nu_pre and nu_post: cells of aspect ratio up to 3 defeat point smoothers, and a
+// line step smooths like two of their sweeps); coarse grids keep every other node
+// and rediscretise L; the prolongation interpolates linearly in the coordinates and the restriction
 // is its transpose weighted by the control volumes (x_{i+1} - x_{i-1})/2 per
 // direction, for the residual and for M.  Levels of N <= 64 run in one
 // workgroup in LDS down to the single interior node of the 2-cell grid.  The
@@ -532,9 +533,11 @@ __device__ __forceinline__ void nu_lds_lines(double* U, const double* F, const d
 // The V-cycle from level n0 (<= kNuCoarse) down to 2 cells in one workgroup,
 // in LDS: u (the initial iterate), F and M of level n0 come from global memory
 // (pitch), u goes back.  tab: the tables of the levels from n0 on, one after the
-// other; fac[q]: the factors of chain level q.
+// other; fac[q]: the factors of chain level q; pre, post: line steps on each level
+// before and after the coarse correction.
 struct NuChain {
     NuFac f[6][2];
+    int pre, post;
 };
 template <bool HELM, int n>
 __device__ void nu_chain_level(double* U, double* F, double* M, const double* tab, const NuChain& ch, int q) {
@@ -545,7 +548,7 @@ __device__ void nu_chain_level(double* U, double* F, double* M, const double* ta
         if (tid == 0) U[4] = F[4] / nu_diag(HELM ? M[4] : 0.0, NuRow(t.cx, 2, 1), NuRow(t.cy, 2, 1));
         __syncthreads();
     } else {
-        nu_lds_lines<n, HELM>(U, F, M, t, ch.f[q]);
+        for (int k = 0; k < ch.pre; ++k) nu_lds_lines<n, HELM>(U, F, M, t, ch.f[q]);
         double *Uc = U + W * W, *Fc = F + W * W;
         // one coarse row per n lanes, lane = fine column (as k_nu_restrict): the
         // coarse boundary is 0
@@ -584,7 +587,7 @@ __device__ void nu_chain_level(double* U, double* F, double* M, const double* ta
             U[j * W + i] += prolong_at(Uc, Wc, i, j, t.px, t.py);
         }
         __syncthreads();
-        nu_lds_lines<n, HELM>(U, F, M, t, ch.f[q]);
+        for (int k = 0; k < ch.post; ++k) nu_lds_lines<n, HELM>(U, F, M, t, ch.f[q]);
     }
 }
 
@@ -901,6 +904,8 @@ extern "C" wandqs_status wandqs_nu_mg_solve(wandqs_ctx* c, const double* h_x, co
         WQ_KLAUNCH(ps, k_nu_factor, dim3((N + kFacLines - 1) / kFacLines, 2 * (nlev - 1)), dim3(256), 0, s, fa);
     }
     NuChain ch{};
+    ch.pre = (c->cfg.nu_pre + 1) / 2;
+    ch.post = (c->cfg.nu_post + 1) / 2;
     for (int q = 0; lc + q < nlev - 1 && q < 6; ++q)
         for (int d = 0; d < 2; ++d) ch.f[q][d] = fac[lc + q][d];
     double* hn = c->h_pin + kMaxSlots * kNormVec + 16;  // [F^2, u^2, max d, -, r^2, u^2, -]
