@@ -582,7 +582,7 @@ namespace {
 // |kr - i gam| at most, as -L_h > 0.  A V-cycle gains a factor 20 to 25 and takes
 // 95 us at 512^2, an iteration 23 us, so the iterations are taken up to rho = 0.4, where they gain
 // as much per time, if mg_max_cycles leaves room for the count that rho ensures
-// (to 1e-16).  An unbounded or undefined k goes to the V-cycles.
+// (to 1e-16).
 constexpr double kLasDirectRho = 0.4;
 struct LasShift {
     bool direct;
@@ -616,6 +616,13 @@ wandqs_status laser_plane_advance(wandqs_ctx* c, double dt, const double* chi, i
     double* hn = c->h_pin + kMaxSlots * kNormVec + 8;  // as k_las_norm
     wandqs_status s;
     if ((s = las_norms(c, u, c->las_f[0], c->las_k[0], hn)) != WANDQS_OK) return s;
+    // an undefined or unbounded chi or envelope (min and max of Re k pass over NaN)
+    for (int q = 0; q < 4; ++q)
+        if (!std::isfinite(hn[q])) {
+            if (cycles) *cycles = 0;
+            c->err = "laser envelope: the plane's equation is not finite";
+            return WANDQS_E_NOCONV;
+        }
     const LasShift sh = las_shift(c, hn[6], hn[7], gam);
     if (!sh.direct)
         for (int l = 1; l <= c->las_ll; ++l) {
@@ -669,11 +676,11 @@ wandqs_status laser_plane_advance(wandqs_ctx* c, double dt, const double* chi, i
         }
     }
     if (cycles) *cycles = cyc;
-    c->las_pred[sh.direct] = cyc;
     if (!(std::isfinite(rn[0]) && std::isfinite(rn[1]) && done[0] && done[1])) {
         c->err = "laser envelope: multigrid did not converge";
         return WANDQS_E_NOCONV;
     }
+    c->las_pred[sh.direct] = cyc;
     return WANDQS_OK;
 }
 
