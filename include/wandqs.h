@@ -284,11 +284,11 @@ wandqs_status wandqs_driver_set(wandqs_ctx* ctx, int64_t n, const double* d_stat
  * beta = 4/(dt dxi0), gam = 4 k0/dt, a1 = 0 on the boundary, by multigrid
  * with the context's mg_* stop rule, from the guess a0; chi = n* / (1 + psi)
  * is the plasma's susceptibility.  On grids of 128^2 .. 2048^2 a plane whose
- * chi varies over its nodes by no more than 0.4 |kbar| on either side of the
- * middle of its range, kbar = that middle + beta - i gam, is solved by
- * iterations with an exact FP64 sine-transform solve of L_h - kbar instead of
- * V-cycles (where mg_max_cycles leaves room for them), to the same stop rule; an
- * iteration then counts as a cycle.
+ * chi varies over its nodes by no more than 0.4 |kbar| (0.1 |kbar| at 2048^2)
+ * on either side of the middle of its range, kbar = that middle + beta - i gam,
+ * is solved by iterations with an exact FP64 sine-transform solve of L_h - kbar
+ * instead of V-cycles (where mg_max_cycles leaves room for them), to the same
+ * stop rule; an iteration then counts as a cycle.
  *
  * wandqs_laser_advance(dt, d_chi, h_cycles) advances every plane by dt > 0
  * with chi given on the device as [laser_nz][N+1][N+1] doubles (NULL:

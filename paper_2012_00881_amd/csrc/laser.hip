@@ -579,18 +579,22 @@ namespace {
 // sine-transform iteration inverts exactly (las_fst_iteration), only by k - kbar:
 // with kbar = kr - i gam, kr the middle of Re k's range on the interior nodes, an
 // iteration multiplies the residual's 2-norm by rho = (half the range) /
-// |kr - i gam| at most, as -L_h > 0.  A V-cycle gains a factor 20 to 25 and takes
-// 95 us at 512^2, an iteration 23 us, so the iterations are taken up to rho = 0.4, where they gain
-// as much per time, if mg_max_cycles leaves room for the count that rho ensures
-// (to 1e-16).
-constexpr double kLasDirectRho = 0.4;
+// |kr - i gam| at most, as -L_h > 0.  The iterations are taken up to the rho at
+// which a smooth chi over the whole range makes them as slow as the V-cycles, if
+// mg_max_cycles leaves room for the count that rho ensures (to 1e-16).  Measured a
+// plane, iterations against V-cycles, at rho = 0.39: 422 / 621 us at 128^2, 492 / 830
+// at 256^2, 662 / 1107 at 512^2, 1544 / 1751 at 1024^2, but 7731 / 4241 at 2048^2,
+// where a row takes all registers of a SIMD (one wavefront in flight) and an
+// iteration 0.74 of a V-cycle's time instead of 0.35 at 1024^2; there 5626 / 4174 at
+// 0.25, 3420 / 3850 at 0.08.
+constexpr double las_direct_rho(int N) { return N > 1024 ? 0.1 : 0.4; }
 struct LasShift {
     bool direct;
     double kr;
 };
 LasShift las_shift(const wandqs_ctx* c, double kmin, double kmax, double gam) {
     const double kr = 0.5 * (kmin + kmax), rho = 0.5 * (kmax - kmin) / std::hypot(kr, gam);
-    if (!c->fst_top_tw || !(kr >= 0.0) || !(rho <= kLasDirectRho)) return {false, 0.0};
+    if (!c->fst_top_tw || !(kr >= 0.0) || !(rho <= las_direct_rho(c->N))) return {false, 0.0};
     const double need = rho > 1e-16 ? std::ceil(std::log(1e-16) / std::log(rho)) : 1.0;
     return {need + 2.0 <= c->cfg.mg_max_cycles, kr};
 }
