@@ -26,7 +26,7 @@
 // through LDS (one pad slot per 16 doubles) with no workgroup barrier, since a
 // wavefront's LDS operations complete in order.  Three launches; T1 and T2 are
 // stored transposed, so that every pass reads whole rows and only the writes
-// of the first two are scattered (two rows per workgroup, written in pairs):
+// of the first two are scattered (two or four rows per workgroup, written together):
 //   x: row g of f -> column g of T1 (T1[k-1][g-1] = coefficient k);
 //   y: row k-1 of T1 -> transform, divide by lambda, transform back ->
 //      column k-1 of T2 (T2[j-1][k-1], j the y-node);
@@ -446,7 +446,9 @@ __global__ __launch_bounds__(64 * RW, (LOGN == 10 ? 2 : 1)) void k_fst(FstArgs<E
 // Rows per workgroup of the x and y passes, whose transposed writes then go
 // out in 16-byte pieces: TOP at n = 512 measured 6.3 / 7.1 us with 2 rows, 6.9 /
 // 7.6 with 1 and 8.2 / 7.8 with 4; at n = 1024, where the writes count more, 4
-// rows 16.1 / 21.4, 2 rows 18.0 / 24.2 (the same bits in every case)
+// rows 16.1 / 21.4, 2 rows 18.0 / 24.2; at n = 2048 the x and y passes below a
+// finest level of 4096^2 37.6 / 64.2 with 4 rows, 43.1 / 74.0 with 2 and 62.4 /
+// 82.4 with 1 (the same bits in every case)
 #ifndef WQ_FST_ROWS
 #define WQ_FST_ROWS 2
 #endif
@@ -454,7 +456,7 @@ __global__ __launch_bounds__(64 * RW, (LOGN == 10 ? 2 : 1)) void k_fst(FstArgs<E
 template <typename E, int LOGN, bool TOP>
 void launch_fst(wandqs_ctx* c, const FstArgs<E>& a, int R, const char* tname) {
     constexpr int n = 1 << LOGN;
-    constexpr int RW = LOGN == 10 ? 2 * WQ_FST_ROWS : LOGN < 10 ? WQ_FST_ROWS : 1;
+    constexpr int RW = LOGN >= 10 ? 2 * WQ_FST_ROWS : WQ_FST_ROWS;
     const dim3 g(n - 1, R), gw((n - 1 + RW - 1) / RW, R);
     const double nodes = (double)(n - 1) * (n - 1) * R;
     const double eb = sizeof(E);
