@@ -108,29 +108,76 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const int32_t* __r
     if (threadIdx.x == kScanThreads - 1) blk[blockIdx.x] = tot[kScanThreads - 1];
 }
 
-// Phase 2: block b adds the totals of the blocks before it (which it sums for
-// itself: a launch that scans the totals first cost 4 us a slice, reading them
-// nb times over is 4 MB at 1024^2) to its kScanBlock items; the last one writes
-// the grand total to out[n].
+// Phase 2: block b adds the totals of the blocks before it to its kScanBlock items.
+// Up to kScanOwnMax blocks it sums them for itself and the last block writes the grand
+// total to out[n] (at 1024^2, 512 blocks that read 0.5 MB of totals: 4.5 us, the two
+// launches 8.5); with more, whose reads would grow with their square (134 MB at
+// 4096^2, 8192 blocks: 67.6 us), k_scan_top has made the sums: 10.3 us both at 2048^2
+// (2048 blocks), 29.5 at 4096^2.
+constexpr int kScanOwnMax = 1024;
+template <bool OWN>
 __global__ __launch_bounds__(kScanThreads) void k_scan_add(int32_t* __restrict__ out, int n,
                                                            const int32_t* __restrict__ blk) {
     __shared__ int32_t part[kScanThreads / 64];
-    const int b = blockIdx.x, base = b * kScanBlock + threadIdx.x * kScanItems;
+    const int b = blockIdx.x, base = b * kScanBlock + threadIdx.x;
     int32_t v[kScanItems];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) v[k] = out[min(base + k, n - 1)];
+    for (int k = 0; k < kScanItems; ++k) v[k] = out[min(base + k * kScanThreads, n - 1)];
     int32_t s = 0;
-    for (int k = threadIdx.x; k < b; k += kScanThreads) s += blk[k];
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    s = 0;
+    if constexpr (OWN) {
+        for (int k = threadIdx.x; k < b; k += kScanThreads) s += blk[k];
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+        __syncthreads();
+        s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanThreads / 64; ++k) s += part[k];
+        for (int k = 0; k < kScanThreads / 64; ++k) s += part[k];
+    } else {
+        s = blk[b];
+    }
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) out[base + k] = v[k] + s;
-    if (b == (int)gridDim.x - 1 && threadIdx.x == 0) out[n] = s + blk[b];
+        if (base + k * kScanThreads < n) out[base + k * kScanThreads] = v[k] + s;
+    if (OWN && b == (int)gridDim.x - 1 && threadIdx.x == 0) out[n] = s + blk[b];
+}
+
+// The blocks' totals to the sums of those before them, the grand total to out[n]:
+// one workgroup, kScanItems totals a thread and trip.
+constexpr int kScanTopThreads = 1024;
+__global__ __launch_bounds__(kScanTopThreads) void k_scan_top(int32_t* __restrict__ blk, int nb,
+                                                              int32_t* __restrict__ out, int n) {
+    constexpr int NW = kScanTopThreads / 64;
+    __shared__ int32_t part[NW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int32_t carry = 0;
+    for (int b0 = 0; b0 < nb; b0 += kScanTopThreads * kScanItems) {
+        const int base = b0 + threadIdx.x * kScanItems;
+        int32_t v[kScanItems], s = 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) v[k] = base + k < nb ? blk[base + k] : 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) s += v[k];
+        int32_t incl = s;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t t = __shfl_up(incl, off, 64);
+            incl += lane >= off ? t : 0;
+        }
+        if (lane == 63) part[w] = incl;
+        __syncthreads();
+        int32_t run = carry + incl - s;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            if (k < w) run += part[k];
+            carry += part[k];
+        }
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            if (base + k < nb) blk[base + k] = run;
+            run += v[k];
+        }
+        __syncthreads();  // part is read before the next trip writes it
+    }
+    if (threadIdx.x == 0) out[n] = carry;
 }
 
 // Scatter: count[] is consumed back to zero, ready for the next slice.  One
@@ -749,9 +796,17 @@ wandqs_status slice_sort(wandqs_ctx* c) {
         WQ_KLAUNCH(ps, k_scan_blocks, dim3(nb), dim3(kScanThreads), 0, s, c->cell_count, ncell,
                            c->cell_start, c->scan_blk);
     }
+    const bool own = nb <= kScanOwnMax;
+    if (!own) {
+        ProfScope ps(c, "k_scan_top", 8.0 * nb);
+        WQ_KLAUNCH(ps, k_scan_top, dim3(1), dim3(kScanTopThreads), 0, s, c->scan_blk, nb, c->cell_start, ncell);
+    }
     {
         ProfScope ps(c, "k_scan_add", (double)ncell * 8.0);
-        WQ_KLAUNCH(ps, k_scan_add, dim3(nb), dim3(kScanThreads), 0, s, c->cell_start, ncell, c->scan_blk);
+        if (own)
+            WQ_KLAUNCH(ps, k_scan_add<true>, dim3(nb), dim3(kScanThreads), 0, s, c->cell_start, ncell, c->scan_blk);
+        else
+            WQ_KLAUNCH(ps, k_scan_add<false>, dim3(nb), dim3(kScanThreads), 0, s, c->cell_start, ncell, c->scan_blk);
     }
     {
         ProfScope ps(c, "k_scatter", (double)c->P * 12.0 + (double)ncell * 8.0);
