@@ -1036,8 +1036,10 @@ extern "C" wandqs_status wandqs_nu_mg_solve(wandqs_ctx* c, const double* h_x, co
     }
     if ((st = pack_fields(c, c->fields, 1, d_u)) != WANDQS_OK) return st;
     // no infinities or NaN stay in the arrays lent to the factors (their
-    // padding is read and masked by a product with 0 once they hold fields again)
-    for (int q = 0; q < used && !std::isfinite(rn); ++q)
+    // padding is read and masked by a product with 0 once they hold fields again):
+    // a cycle with undefined factors leaves an undefined residual; without a cycle
+    // nothing has told of them
+    for (int q = 0; q < used && !(cyc > 0 && std::isfinite(rn)); ++q)
         if ((st = fill_f64(c, pool[q], cap, 0.0)) != WANDQS_OK) return st;
     WQ_HIP(hipStreamSynchronize(s));
     if (h_cycles) *h_cycles = cyc;
