@@ -11,8 +11,12 @@
 //             correction, nu2 sweeps, write the tile;
 //     the halo (2 nu + 2 nodes) makes the tile result identical to a global
 //     red-black sweep, so every node array is read and written once per pass;
-//   * the levels N <= 64 run inside one workgroup in LDS (one workgroup per
-//     right-hand side), the 2x2-cell grid solved exactly.
+//   * the levels N <= 64 of a Helmholtz cycle, and whole grids that small, run in
+//     registers inside one workgroup per right-hand side, down to the 2x2-cell grid,
+//     which is solved exactly;
+//   * a Poisson cycle ends on the level below the finest (64^2 .. 2048^2) with an exact
+//     sine-transform solve; to a tolerance, grids up to 2048^2 take that solve on the
+//     finest level itself and no V-cycles at all (direct_poisson).
 // Two right-hand sides with one operator (Ez, Bz and Bx, By) share each pass.
 // All reductions (residual norms) have a fixed order: results are bitwise
 // reproducible.
@@ -1120,11 +1124,10 @@ __global__ __launch_bounds__(64 * NW) void k_mg_updown_reg(FuseArgs<E> a) {
 // no LDS but the row that crosses to the next wavefront or group.
 //
 // What bounds it is the serial chain of half sweeps and transfers of one
-// workgroup per right-hand side, and its loads: 11.6 us per V-cycle and launch in
-// float, 15.4 in double, about 6 for each further cycle of a launch (every level
-// in LDS with a workgroup barrier per half sweep and one cycle per launch: 22.2
-// and 28.3).  Four wavefronts: with eight the double form spills (19.7 us, float
-// 12.1).
+// workgroup per right-hand side, and its loads: 12.0 us for a launch of one V(1, 2)
+// in float, 14.8 in double, 15.4 and 20.0 with two V(1, 1) (every level in LDS with a
+// workgroup barrier per half sweep and one cycle per launch: 22.2 and 28.3).  Four
+// wavefronts: with eight the double form spills (19.7 us for one cycle, float 12.1).
 constexpr int kCoarseWaves = 4;
 static_assert(kCoarseMax == 64, "the coarse kernel holds levels up to 64 cells a side");
 
@@ -1351,7 +1354,7 @@ struct CoarseWave {
         if constexpr (n == 4) {
             // 2 x 2 cells: one unknown, four zero neighbours, solved in double.  (The
             // cycle has to end exactly: four over-relaxed sweeps on the 8-cell level
-            // in place of the levels below it take 1.2 us less a launch, but
+            // in place of the levels below it take 1.2 us less a launch of two cycles, but
             // where k2 is close to 0 they leave 0.7 of the worst error and a cycle
             // then gains 8 instead of 30.)
             const double f2 = (double)__shfl(v[0], 4 + 2, 64), H = 2.0 * h;

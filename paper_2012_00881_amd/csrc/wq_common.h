@@ -171,7 +171,8 @@ struct CycleKey {
     const void* p[5];
     int R, helm, mixed, slot, upslot;
     int fuse;  // 1: the level-0 down pass was fused into the last cycle; 2: the
-               // level-0 up pass fuses with the next down pass; 4: um2 is current
+               // level-0 up pass fuses with the next down pass; 4: um2 is current;
+               // 8: an iteration of the exact solve instead of a V-cycle
     bool operator==(const CycleKey& o) const {
         for (int i = 0; i < 5; ++i)
             if (p[i] != o.p[i]) return false;
